@@ -77,6 +77,20 @@ __device__ __forceinline__ int wave_min_i(int v, int lane) {
   return v;
 }
 
+// Number of values of the ascending list x[0, n) below v, by the whole wave: 64 probes of the list per
+// round (two dependent loads for up to 4096 values, three for 262144; a binary search takes 12 and 18).
+__device__ __forceinline__ int lower_bound_wave(const int32_t* x, int n, int v, int lane) {
+  int lo = 0;   // x[lo - 1] < v <= x[lo + n]
+  while (n > 0) {
+    const int step = (n + 63) >> 6;
+    const int i = (lane + 1) * step - 1;   // last of this lane's values
+    const int below = __popcll(__ballot(i < n && x[lo + i] < v));
+    lo += below * step;
+    n = min(n - below * step, step - 1);
+  }
+  return lo;
+}
+
 // Pool offset (elements) of (slot, head) in a [blocks][Hkv][16][D] pool.
 __device__ __forceinline__ int64_t pool_off(int32_t slot, int head, int Hkv, int D) {
   return ((((int64_t)(slot >> 4)) * Hkv + head) * 16 + (slot & 15)) * (int64_t)D;
