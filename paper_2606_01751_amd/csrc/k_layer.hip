@@ -11,6 +11,8 @@
 // Rows: for request r, the listed rows n < n_rows[r] of the row-list layout.  An operand row is
 // addressed by slot (off_r + n: compact per request, like the sparse attention output) or by
 // token (off_r + rows[off_r + n]: the request's token rows, like fresh Q/K/V and hidden states).
+#include <type_traits>
+
 #include "sx_device.h"
 #include "sx_internal.h"
 
@@ -30,20 +32,24 @@ __device__ __forceinline__ int64_t row_index(const ReqDev& rq, const int32_t* ro
 }
 
 // ---------------------------------------------------------------------------------------------
-// GEMM on listed rows.  Computed transposed, Y^T = W X^T: the MFMA A operand is a slice of W (MF
-// output features), the B operand a slice of X^T (MF rows), so each lane owns one row of the
+// GEMM on listed rows.  Computed transposed, Y^T = W X^T: the MFMA A operand is a slice of W (16
+// output features), the B operand a slice of X^T (16 rows), so each lane owns one row of the
 // result and writes 4 consecutive features per store.
-// Workgroup tile: 256 features x 256 rows; 8 waves as 4 (features) x 2 (rows), a wave owns 64
-// features x 128 rows.  The default MFMA is v_mfma_f32_16x16x32_bf16 (4 x 8 accumulators of
-// 16 x 16): measured 1-12 % faster than v_mfma_f32_32x32x16_bf16 (MF = 32, 2 x 4 accumulators)
-// on the same tiles, most on the narrow products.  The k dimension moves in stages of BK
-// through NST LDS buffers: both operand tiles go global -> LDS directly (16 bytes per lane);
-// stage t + NST is issued once every wave has read stage t, so a stage has about NST - 1 stages
-// of compute to land.  A tile row (BK bf16) holds BK / 8 chunks of 16 bytes, XOR-swizzled per row
-// (chunk_swz) so that the rows a read instruction touches at one logical chunk hit distinct banks.
+// Workgroup tile: BN features x BM rows; WN x WM x WK waves, a wave owns BN / WN features x BM / WM
+// rows of every WK-th 64-wide piece of k.  The MFMA is v_mfma_f32_16x16x32_bf16: measured 1-12 %
+// faster than v_mfma_f32_32x32x16_bf16 on the same tiles, most on the narrow products.  The k
+// dimension moves in stages of WK pieces through NST LDS buffers: both operand tiles go global -> LDS
+// directly (16 bytes per lane); stage t + NST is issued once its readers have read stage t, so a stage
+// has about NST - 1 stages of compute to land.  A tile row (64 bf16) holds 8 chunks of 16 bytes,
+// XOR-swizzled per row (chunk_swz) so that the rows a read instruction touches at one logical chunk hit
+// distinct banks.  The WK partial sums are added through LDS in order.
+// Matrix-core bound on 256 x 256 tiles with many rows (gate_up of 6712 rows, 4096 -> 28672: 1252 us,
+// 1.26 PFLOP/s, 1370 with a stage's transfers issued together); with few rows a tile per compute unit
+// bounds it (see the dispatch).
 // ---------------------------------------------------------------------------------------------
-constexpr int GBN = 256, GBM = 256;
 constexpr int kGemmMaxParts = 4;
+constexpr int kGemmGM = 8;          // row tiles per group of the tile order
+constexpr int kGemmPart = 256;      // widths are multiples of this (a tile lies in one output part)
 constexpr unsigned kGemmXcds = 8;   // XCDs of the chip, which deals workgroups round-robin
 constexpr int kSgMfma = 0x8, kSgDsRead = 0x100;   // sched_group_barrier instruction classes
 
@@ -59,245 +65,246 @@ struct GemmRowsK {
   int n_parts, K, N, n_req, m_tiles, max_rows, x_tok, y_tok;
 };
 
-// physical chunk of logical chunk c in tile row `row` (CH chunks per row): 16 consecutive rows
+// physical chunk of logical chunk c in tile row `row` (8 chunks per row): 16 consecutive rows
 // read at one logical chunk cover the 16 four-bank groups of a 256-byte LDS line
-template <int CH>
-__device__ __forceinline__ int chunk_swz(int c, int row) {
-  if constexpr (CH == 8) return c ^ ((row >> 1) & 7);   // 128-byte rows: two per line
-  else return c ^ ((row >> 2) & 3);                     // 64-byte rows: four per line
-}
+__device__ __forceinline__ int chunk_swz(int c, int row) { return c ^ ((row >> 1) & 7); }   // (two rows per line)
 
-template <int BK, int NST, int GM, int NW, int MF>
-__global__ __launch_bounds__(NW * 64, 1) void gemm_rows_kernel(GemmRowsK a) {
-  // NW = 8: a wave owns 64 features x 128 rows (two waves per SIMD); NW = 4: 128 x 128 (one wave
-  // per SIMD, the accumulators in the AGPR half of the register file; measured about 10 % slower)
-  // MF = 32: v_mfma_f32_32x32x16_bf16 (32 x 32 blocks, k 16); MF = 16: v_mfma_f32_16x16x32_bf16
-  constexpr int WCOL = NW / 2;                 // waves across the features
-  constexpr int FI = 256 / WCOL / MF;          // MF-feature fragments per wave
-  constexpr int RJ = 128 / MF;                 // MF-row fragments per wave
-  constexpr int KM = MF == 32 ? 16 : 32;       // k per MFMA
-  typedef float accv_t __attribute__((ext_vector_type(MF == 32 ? 16 : 4)));
-  constexpr int ROWB = BK * 2;                 // bytes of one tile row
+template <int BN, int BM, int WN, int WM, int WK, int NST>
+__global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRowsK a) {
+  constexpr int NG = WN * WM;                  // waves that share a piece of k
+  constexpr int FI = BN / WN / 16;             // 16-feature fragments per wave
+  constexpr int RJ = BM / WM / 16;             // 16-row fragments per wave
+  constexpr int ROWB = 128;                    // bytes of one tile row (64 bf16)
   constexpr int CH = ROWB / 16;                // 16-byte chunks per row
-  constexpr int TILE = 256 * ROWB;             // bytes of one operand tile
-  constexpr int RPP = 1024 / ROWB;             // rows per 1 KB transfer
-  constexpr int PPW = 256 / RPP / NW;          // transfers per wave per operand tile
-  constexpr int NS = BK / KM;                  // k slices (one MFMA deep) per stage
-  __shared__ __attribute__((aligned(1024))) char smem[NST * 2 * TILE];   // [stage][W | X]
+  constexpr int RPT = 1024 / ROWB;             // rows per 1 KB transfer
+  constexpr int PIECE = (BN + BM) * ROWB;      // one piece of both operands
+  constexpr int STAGE = WK * PIECE;
+  constexpr int PW = BN / RPT / NG, PX = BM / RPT / NG;   // transfers per wave and operand
+  static_assert(PW * NG * RPT == BN && PX * NG * RPT == BM, "transfers spread evenly over the waves");
+  static_assert(kGemmPart % BN == 0, "a tile lies in one output part");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];   // [stage][piece][W | X]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31;
-  const int hg = lane >> 5;
-  // tile order: groups of GM row tiles, the feature tile slowest within a group, so that a run of
-  // consecutive tile indices covers a few feature tiles x GM row tiles.  The hardware deals block b
-  // to XCD b mod 8; each XCD takes a contiguous run of tile indices, so the workgroups running
-  // together on one XCD read the same W and X k-slices through that XCD's L2.
+  const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wall / NG, wu = wall % NG;
+  // tile order: groups of kGemmGM row tiles, the feature tile slowest within a group, so that a run of
+  // consecutive tile indices covers a few feature tiles x all row tiles of the group.  The hardware
+  // deals block b to XCD b mod 8; each XCD takes a contiguous run of tile indices, so the workgroups
+  // running together on one XCD read the same W and X k-slices through that XCD's L2.
   const int n_mt = a.n_req * a.m_tiles;
-  const int n_nt = a.N / GBN;
+  const int n_nt = a.N / BN;
   const unsigned per_xcd = gridDim.x / kGemmXcds;   // the grid is a multiple of kGemmXcds
   const int L = (int)((blockIdx.x % kGemmXcds) * per_xcd + blockIdx.x / kGemmXcds);
   if (L >= n_mt * n_nt) return;
-  const int grp = L / (GM * n_nt);
-  const int in_g = L - grp * GM * n_nt;
-  const int gm = min(GM, n_mt - grp * GM);
-  const int mt_all = grp * GM + in_g % gm;
+  const int grp = L / (kGemmGM * n_nt);
+  const int in_g = L - grp * kGemmGM * n_nt;
+  const int gm = min(kGemmGM, n_mt - grp * kGemmGM);
+  const int mt_all = grp * kGemmGM + in_g % gm;
   const int nt = in_g / gm;
   const int r = mt_all / a.m_tiles;
-  const int m0 = (mt_all - r * a.m_tiles) * GBM;
+  const int m0 = (mt_all - r * a.m_tiles) * BM;
   const ReqDev rq = a.reqs[r];
   const int nr = min(a.n_rows[r], a.max_rows);
   if (m0 >= nr) return;
-  const int n0 = nt * GBN;
+  const int n0 = nt * BN;
   const int K = a.K;
 
-  // ---- transfers: piece q (1 KB) of a tile holds rows RPP q .. RPP q + RPP - 1; lane l fills row
-  // RPP q + l / CH, physical chunk l % CH with the logical chunk that chunk_swz maps there.  A wave
-  // moves pieces wu + 8 i (i < PPW) of both tiles. ----
-  const uint16_t* w_src[PPW];
-  const uint16_t* x_src[PPW];
+  // ---- transfers: 1 KB holds rows RPT q .. RPT q + RPT - 1 of a tile; lane l fills row RPT q + l / CH,
+  // physical chunk l % CH with the logical chunk that chunk_swz maps there.  A wave moves transfers
+  // wu + NG i of both tiles of its group's piece. ----
+  const uint16_t* src[PW + PX];
 #pragma unroll
-  for (int i = 0; i < PPW; ++i) {
-    const int row = RPP * (wu + NW * i) + lane / CH;
-    const int lc = chunk_swz<CH>(lane % CH, row);   // (the swizzle is an involution)
-    w_src[i] = a.w + (int64_t)(n0 + row) * K + lc * 8;
-    const int m = min(m0 + row, nr - 1);   // rows past the request's last read a valid row
-    x_src[i] = a.x + row_index(rq, a.rows, m, a.x_tok) * K + lc * 8;
+  for (int i = 0; i < PW; ++i) {
+    const int row = RPT * (wu + NG * i) + lane / CH;
+    src[i] = a.w + (int64_t)(n0 + row) * K + wk * 64 + chunk_swz(lane % CH, row) * 8;   // (an involution)
   }
-  const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-  auto dma16 = [&](const void* src, uint32_t lds) {
-    const uint32_t m0r = __builtin_amdgcn_readfirstlane(lds);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(m0r) : "m0", "memory");
-  };
-  const int nk = K / BK;
-  auto issue = [&](int t) {   // stage t into buffer t mod NST
-    if (t >= nk) return;
-    const uint32_t base = smem_lds + (uint32_t)((t % NST) * 2 * TILE);
-    const int k0 = t * BK;
 #pragma unroll
-    for (int i = 0; i < PPW; ++i) {
-      dma16(w_src[i] + k0, base + (uint32_t)((wu + NW * i) * 1024));
-      dma16(x_src[i] + k0, base + (uint32_t)(TILE + (wu + NW * i) * 1024));
-    }
+  for (int i = 0; i < PX; ++i) {
+    const int row = RPT * (wu + NG * i) + lane / CH;
+    const int m = min(m0 + row, nr - 1);   // rows past the request's last read a valid row
+    src[PW + i] = a.x + row_index(rq, a.rows, m, a.x_tok) * K + wk * 64 + chunk_swz(lane % CH, row) * 8;
+  }
+  const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)(wk * PIECE);
+  // stages of the workgroup, and those that hold a piece for this wave's group (a group may have one
+  // fewer when the pieces do not divide by WK)
+  const int nT = (K / 64 + WK - 1) / WK;
+  const int nk = (K / 64 - wk + WK - 1) / WK;
+  // transfer d of this wave for stage t, into buffer t mod NST
+  auto dma = [&](int t, int d) {
+    const uint32_t m0r = __builtin_amdgcn_readfirstlane(smem_lds + (uint32_t)((t % NST) * STAGE) +
+                                                        (uint32_t)(d < PW ? (wu + NG * d) * 1024 : BN * ROWB + (wu + NG * (d - PW)) * 1024));
+    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src[d] + t * WK * 64), "s"(m0r) : "m0", "memory");
   };
   // wait until this wave's transfers of every stage before the n youngest have landed
   auto wait_stages = [&](int n) {
-    switch (n * 2 * PPW) {
-      case 0: SX_WAIT_VMCNT6(0); break;
-      case 4: SX_WAIT_VMCNT6(4); break;
-      case 8: SX_WAIT_VMCNT6(8); break;
-      case 12: SX_WAIT_VMCNT6(12); break;
-      case 16: SX_WAIT_VMCNT6(16); break;
-      case 24: SX_WAIT_VMCNT6(24); break;
-      default: SX_WAIT_VMCNT6(32); break;
+    constexpr int P = PW + PX;
+    static_assert((NST - 1) * P < 64 && NST <= 4, "wait table");
+    switch (n) {
+      case 1: SX_WAIT_VMCNT6(P); break;
+      case 2: SX_WAIT_VMCNT6(2 * P & 63); break;
+      case 3: SX_WAIT_VMCNT6(3 * P & 63); break;
+      default: SX_WAIT_VMCNT6(0); break;
     }
   };
-  static_assert((NST - 1) * 2 * PPW <= 32 && (2 * PPW) % 4 == 0, "wait table");
-  static_assert(NS % 2 == 0, "a stage holds an even number of slices");
+  // Before stage t is read: this wave's transfers of it have landed (the younger ones may be in flight),
+  // its reads of the stages before are done (the barrier alone does not wait for them), and so are the
+  // other waves' of the group (one wave needs no barrier); past it the buffer of stage t - 1 is free.
+  auto enter_stage = [&](int t) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wait_stages(min(NST - 2, nk - 1 - t));
+    if constexpr (NG > 1) __syncthreads();
+  };
 
-  // ---- operand reads: row 32 j + l32 of a tile, logical chunk 2 s + hg: the lane part depends on
-  // s only, the row block adds a constant (an immediate offset) ----
-  const int wn = wu % WCOL, wm = wu / WCOL;
-  // a lane reads row lr of each MF-row fragment, 16 bytes of k starting at chunk (KM / 8) s + cg
-  const int lr = lane % MF, cg = lane / MF;
-  uint32_t lane_off[NS];
+  // ---- operand reads: a lane reads row lr of each 16-row fragment, 16 bytes of k starting at chunk
+  // 4 s + cg: the lane part depends on s only, the fragment adds a constant (an immediate offset) ----
+  const int wn = wu % WN, wm = wu / WN;
+  const int lr = lane % 16, cg = lane / 16;
+  uint32_t lane_off[2];
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
-    lane_off[s] = (uint32_t)(lr * ROWB + (chunk_swz<CH>((KM / 8) * s + cg, lr) << 4));
-  accv_t acc[FI][RJ];
+  for (int s = 0; s < 2; ++s) lane_off[s] = (uint32_t)(lr * ROWB + (chunk_swz(4 * s + cg, lr) << 4));
+  f32x4_t acc[FI][RJ];
 #pragma unroll
   for (int i = 0; i < FI; ++i)
 #pragma unroll
-    for (int j = 0; j < RJ; ++j)
-#pragma unroll
-      for (int e = 0; e < (MF == 32 ? 16 : 4); ++e) acc[i][j][e] = 0.f;
+    for (int j = 0; j < RJ; ++j) acc[i][j] = f32x4_t{};
 
-  // fragments of one 16-wide k slice, read from stage buffer `buf`: one base register per matrix
-  // (the empty asm keeps the sums from being re-associated into one register per read), the row
-  // blocks as immediate offsets
-  auto read_slice = [&](int buf, int s, bf16x8_t (&fw)[FI], bf16x8_t (&fx)[RJ]) {
-    const uint32_t sb = smem_lds + (uint32_t)(buf * 2 * TILE);
-    uint32_t wb = sb + lane_off[s] + (uint32_t)(wn * FI * MF * ROWB);
-    uint32_t xb = sb + (uint32_t)TILE + lane_off[s] + (uint32_t)(wm * 128 * ROWB);
-    asm volatile("" : "+v"(wb), "+v"(xb));
+  // Software pipeline over slices: while the MFMAs of a slice run, the fragments of the next one are
+  // read (the row fragments into the registers that the MFMAs have just read for the last time, the
+  // feature fragments into a second set) and, once a stage's buffer is free, the transfers that refill
+  // it are issued one by one between the MFMAs (issued together they hold every wave for as long as half
+  // the stage's MFMAs take: the address unit takes about 22 cycles per transfer and compute unit).  A
+  // stage is entered after the first MFMAs of the slice before it, so that they cover the last reads of
+  // the stage that it ends.  The order is pinned: MFMA m, then the reads and transfers due.
+  bf16x8_t fw[2][FI], fx[RJ];
+  constexpr int NM = FI * RJ, ND = PW + PX;
+  auto lds16 = [](uint32_t addr) { return *(const __attribute__((address_space(3))) bf16x8_t*)(uintptr_t)addr; };
+  // MFMAs of a slice on feature set C; RD: read slice RS of stage rst beside them, EN: entering it
+  // first; DM: refill with stage dst
+  auto phase = [&](auto set, auto rd, auto en, int rst, auto rs, auto dm, int dst) {
+    constexpr int C = decltype(set)::value, RS = decltype(rs)::value;
+    constexpr bool RD = decltype(rd)::value, EN = decltype(en)::value, DM = decltype(dm)::value;
+    constexpr int P0 = EN ? (RJ >= 4 ? 2 : 1) * FI : 0;   // MFMAs before the stage is entered
+    uint32_t wb = 0, xb = 0;
+    if constexpr (RD) {
+      // one base register per matrix (the empty asm keeps the sums from being re-associated into one
+      // register per read), the row blocks as immediate offsets
+      const uint32_t sb = smem_lds + (uint32_t)((rst % NST) * STAGE);
+      wb = sb + lane_off[RS] + (uint32_t)(wn * FI * 16 * ROWB);
+      xb = sb + (uint32_t)(BN * ROWB) + lane_off[RS] + (uint32_t)(wm * RJ * 16 * ROWB);
+      asm volatile("" : "+v"(wb), "+v"(xb));
+    }
 #pragma unroll
-    for (int i = 0; i < FI; ++i)
-      fw[i] = *(const __attribute__((address_space(3))) bf16x8_t*)(uintptr_t)(wb + (uint32_t)(i * MF * ROWB));
+    for (int m = 0; m < NM; ++m) {
+      const int i = m % FI, j = m / FI;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[C][i], fx[j], acc[i][j], 0, 0, 0);
+      if (EN && m == P0 - 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        enter_stage(rst);
+      }
+      if constexpr (RD) {
 #pragma unroll
-    for (int j = 0; j < RJ; ++j)
-      fx[j] = *(const __attribute__((address_space(3))) bf16x8_t*)(uintptr_t)(xb + (uint32_t)(j * MF * ROWB));
+        for (int f = 0; f < FI; ++f)
+          if (m == (P0 + f < NM ? P0 + f : NM - 1)) fw[1 - C][f] = lds16(wb + (uint32_t)(f * 16 * ROWB));
+#pragma unroll
+        for (int f = 0; f < RJ; ++f) {
+          const int at = (f + 1) * FI - 1 > P0 + FI + f ? (f + 1) * FI - 1 : P0 + FI + f;
+          if (m == (at < NM ? at : NM - 1)) fx[f] = lds16(xb + (uint32_t)(f * 16 * ROWB));
+        }
+      }
+      if constexpr (DM) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+          if (m == P0 + (2 * d + 1) * (NM - P0) / (2 * ND) ) dma(dst, d);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-
-  // Software pipeline: the fragments of slice s + 1 are read while the MFMAs of slice s run (two
-  // register sets).  The stage barrier sits before the MFMAs of a stage's last slice: past it every
-  // wave has finished reading the stage (its buffer takes stage t + NST) and stage t + 1 has landed
-  // (its first slice is read during those MFMAs).
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
   // the row indices above are compiler-visible loads: complete before the first transfer wait
   SX_WAIT_VMCNT(0);
 #pragma unroll
-  for (int t = 0; t < NST; ++t) issue(t);
+  for (int t = 0; t < NST; ++t)
+    if (t < nk)
+#pragma unroll
+      for (int d = 0; d < ND; ++d) dma(t, d);
   wait_stages(min(NST - 1, nk - 1));   // stage 0 has landed
-  __syncthreads();
-  bf16x8_t fw[2][FI], fx[2][RJ];
-  auto mfma_slice = [&](int c) {
+  if constexpr (NG > 1) __syncthreads();
+  if (nk > 0) {
+    const uint32_t wb = smem_lds + lane_off[0] + (uint32_t)(wn * FI * 16 * ROWB);
+    const uint32_t xb = smem_lds + (uint32_t)(BN * ROWB) + lane_off[0] + (uint32_t)(wm * RJ * 16 * ROWB);
 #pragma unroll
-    for (int i = 0; i < FI; ++i)
+    for (int j = 0; j < RJ; ++j) fx[j] = lds16(xb + (uint32_t)(j * 16 * ROWB));
 #pragma unroll
-      for (int j = 0; j < RJ; ++j) {
-        if constexpr (MF == 32)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[c][i], fx[c][j], acc[i][j], 0, 0, 0);
-        else
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[c][i], fx[c][j], acc[i][j], 0, 0, 0);
-      }
-  };
-  // the scheduler would sink the reads below the MFMAs (to reuse their registers): pin one read
-  // after each of the first FI + RJ MFMAs
-  auto interleave = [&]() {
-#pragma unroll
-    for (int q = 0; q < FI + RJ; ++q) {
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
+    for (int i = 0; i < FI; ++i) fw[0][i] = lds16(wb + (uint32_t)(i * 16 * ROWB));
+    // stages that refill their buffer, stages that do not, the last one
+    int t = 0;
+    for (; t + NST < nk; ++t) {
+      phase(c0, yes, no, t, c1, no, 0);
+      phase(c1, yes, yes, t + 1, c0, yes, t + NST);
     }
-    __builtin_amdgcn_sched_group_barrier(kSgMfma, FI * RJ - FI - RJ, 0);
-  };
-  read_slice(0, 0, fw[0], fx[0]);
-  for (int t = 0; t + 1 < nk; ++t) {
-#pragma unroll
-    for (int s = 0; s + 1 < NS; ++s) {   // NS is even: a stage starts on set 0
-      read_slice(t % NST, s + 1, fw[(s + 1) & 1], fx[(s + 1) & 1]);
-      mfma_slice(s & 1);
-      interleave();
+    for (; t + 1 < nk; ++t) {
+      phase(c0, yes, no, t, c1, no, 0);
+      phase(c1, yes, yes, t + 1, c0, no, 0);
     }
-    // this wave's reads of stage t are done (the barrier alone does not wait for them) and its
-    // transfers of stage t + 1 have landed (the younger ones may be in flight)
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    wait_stages(max(0, min(NST - 2, nk - 2 - t)));
-    __syncthreads();
-    issue(t + NST);   // into the buffer of stage t
-    read_slice((t + 1) % NST, 0, fw[0], fx[0]);
-    mfma_slice(1);
-    interleave();
+    phase(c0, yes, no, t, c1, no, 0);
+    phase(c1, no, no, 0, c0, no, 0);
   }
-  // last stage
-#pragma unroll
-  for (int s = 0; s + 1 < NS; ++s) {
-    read_slice((nk - 1) % NST, s + 1, fw[(s + 1) & 1], fx[(s + 1) & 1]);
-    mfma_slice(s & 1);
-    interleave();
-  }
-  mfma_slice(1);
+  if (NG > 1 && WK > 1 && nk < nT && nT > 1) __syncthreads();   // (a group with one stage fewer passes as many)
 
-  // ---- epilogue: lane owns row 32 j + l32 of the wave's rows; value e of accumulator (i, j) is
-  // feature 32 i + 8 (e / 4) + 4 hg + e % 4 of the wave's features.  Part boundaries are multiples
-  // of the tile width, so the output part is the tile's. ----
-  // MF = 16: lane owns row 16 j + lr, value e of accumulator (i, j) is feature 16 i + 4 cg + e
-  static_assert(RJ * MF == 128, "two waves of rows cover the 256-row tile");
-  int part = 0;
-  while (part + 1 < a.n_parts && n0 >= a.pn[part + 1]) ++part;
-  uint16_t* const yp = a.y[part];
-  const int ld = a.pn[part + 1] - a.pn[part];
-  const int c0 = n0 - a.pn[part] + wn * FI * MF + 4 * cg;
-#pragma unroll
-  for (int j = 0; j < RJ; ++j) {
-    const int m = m0 + wm * 128 + MF * j + lr;
-    if (m >= nr) continue;
-    const int64_t yr = row_index(rq, a.rows, m, a.y_tok) * ld;
+  // ---- sum over the k groups: every wave leaves its accumulators in LDS and adds up those of its
+  // share of the fragments (FS of them), group by group ----
+  constexpr int FS = FI * RJ / WK;   // fragments a wave finishes
+  static_assert(FS * WK == FI * RJ && (WK == 1 || WK * BN * BM * 4 <= NST * STAGE), "fragments spread evenly and fit the stage buffers");
+  f32x4_t* const part = (f32x4_t*)smem;
+  if constexpr (WK > 1) {
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < FI; ++i)
 #pragma unroll
-      for (int g = 0; g < (MF == 32 ? 4 : 1); ++g) {
-        const int c = c0 + MF * i + 8 * g;
-        float v[4];
+      for (int j = 0; j < RJ; ++j) part[((wk * NG + wu) * FI * RJ + i * RJ + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+  }
+
+  // ---- epilogue: lane owns row 16 j + lr of the wave's rows; value e of accumulator (i, j) is feature
+  // 16 i + 4 cg + e of the wave's features.  Part boundaries are multiples of the tile width, so the
+  // output part is the tile's. ----
+  int op = 0;
+  while (op + 1 < a.n_parts && n0 >= a.pn[op + 1]) ++op;
+  uint16_t* const yp = a.y[op];
+  const int ld = a.pn[op + 1] - a.pn[op];
+  const int col0 = n0 - a.pn[op] + wn * FI * 16 + 4 * cg;
+  const int f0 = WK > 1 ? wk * FS : 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g + e];
-        if (a.res) {
-          const uint2 rv = *(const uint2*)(a.res + yr + c);
-          v[0] += bf16_lo(rv.x);
-          v[1] += bf16_hi(rv.x);
-          v[2] += bf16_lo(rv.y);
-          v[3] += bf16_hi(rv.y);
-        }
-        uint2 o;
-        o.x = pack_bf16x2(v[0], v[1]);
-        o.y = pack_bf16x2(v[2], v[3]);
-        *(uint2*)(yp + yr + c) = o;
-      }
+  for (int f = 0; f < FS; ++f) {
+    // (row major over the fragments that the wave keeps, feature major over a share of them)
+    const int i = WK > 1 ? (f0 + f) / RJ : f % FI, j = WK > 1 ? (f0 + f) % RJ : f / FI;
+    const int m = m0 + wm * RJ * 16 + 16 * j + lr;
+    if (m >= nr) continue;
+    const int64_t yr = row_index(rq, a.rows, m, a.y_tok) * ld + col0 + 16 * i;
+    f32x4_t v;
+    if constexpr (WK > 1) {
+      v = part[(wu * FI * RJ + f0 + f) * 64 + lane];
+#pragma unroll
+      for (int g = 1; g < WK; ++g) v += part[((g * NG + wu) * FI * RJ + f0 + f) * 64 + lane];
+    } else {
+      v = acc[f % FI][f / FI];
+    }
+    if (a.res) {
+      const uint2 rv = *(const uint2*)(a.res + yr);
+      v[0] += bf16_lo(rv.x);
+      v[1] += bf16_hi(rv.x);
+      v[2] += bf16_lo(rv.y);
+      v[3] += bf16_hi(rv.y);
+    }
+    uint2 o;
+    o.x = pack_bf16x2(v[0], v[1]);
+    o.y = pack_bf16x2(v[2], v[3]);
+    *(uint2*)(yp + yr) = o;
   }
 }
-
-#ifndef SX_GEMM_BK
-#define SX_GEMM_BK 64
-#define SX_GEMM_NST 2
-#endif
-#ifndef SX_GEMM_GM
-#define SX_GEMM_GM 8
-#endif
-#ifndef SX_GEMM_NW
-#define SX_GEMM_NW 8
-#endif
-#ifndef SX_GEMM_MF
-#define SX_GEMM_MF 16
-#endif
 
 // ---------------------------------------------------------------------------------------------
 // RMSNorm of listed rows: one wave per row, float32 sum of squares in a fixed order.
@@ -432,6 +439,15 @@ __global__ __launch_bounds__(256) void silu_mul_rows_kernel(const ReqDev* __rest
 
 }  // namespace
 
+template <int BN, int BM, int WN, int WM, int WK, int NST>
+static hipError_t launch_gemm_tiles(GemmRowsK& a, hipStream_t s) {
+  a.m_tiles = (a.max_rows + BM - 1) / BM;
+  const int64_t tiles = (int64_t)a.m_tiles * a.n_req * (a.N / BN);
+  const int64_t blocks = (tiles + kGemmXcds - 1) / kGemmXcds * kGemmXcds;
+  hipLaunchKernelGGL((gemm_rows_kernel<BN, BM, WN, WM, WK, NST>), dim3((unsigned)blocks), dim3(WN * WM * WK * 64), 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_rows(const sx_plan* p, const RowsArg& r, const void* x, int x_tok, const void* w, int k,
                             int n_parts, const int* part_n, void* const* ys, const void* res, int y_tok, hipStream_t s) {
   if (n_parts < 1 || n_parts > kGemmMaxParts) return hipErrorInvalidValue;
@@ -453,15 +469,38 @@ hipError_t launch_gemm_rows(const sx_plan* p, const RowsArg& r, const void* x, i
   a.K = k;
   a.N = n;
   a.n_req = p->n_req;
-  a.m_tiles = (r.max_rows + GBM - 1) / GBM;
   a.max_rows = r.max_rows;
-  constexpr int BK = SX_GEMM_BK, NST = SX_GEMM_NST, GM = SX_GEMM_GM, NW = SX_GEMM_NW, MF = SX_GEMM_MF;
   a.x_tok = x_tok;
   a.y_tok = y_tok;
-  const int64_t tiles = (int64_t)a.m_tiles * p->n_req * (n / GBN);
-  const int64_t blocks = (tiles + kGemmXcds - 1) / kGemmXcds * kGemmXcds;
-  hipLaunchKernelGGL((gemm_rows_kernel<BK, NST, GM, NW, MF>), dim3((unsigned)blocks), dim3(NW * 64), 0, s, a);
-  return hipGetLastError();
+  // The tile whose rounds over the compute units take least: a workgroup per compute unit, and one
+  // 64-wide piece of k costs a round about 1.5 us on 256 x 256 tiles, 0.86 on 256 x 128, 0.60 on
+  // 128 x 128, 0.46 on 128 x 64 and 0.35 on 64 x 64 (measured, K = 4096, weights from HBM; bound by the
+  // LDS reads and transfers between barriers on all but the largest).  So wide products keep the large
+  // tile and few rows take the one that gives every compute unit a tile: the rows' count at which two
+  // neighbours cross depends on the width.  Measured for 384 rows (start: 256 x 256 always), K = 4096:
+  // N = 6144 39 us (101), 4096 30 us (110); K = 14336: N = 4096 95 us (340).
+  struct Shape {
+    int bn, bm;
+    double cost;
+  };
+  static const Shape shapes[] = {{256, 256, 1.5}, {256, 128, 0.86}, {128, 128, 0.60}, {128, 64, 0.46}, {64, 64, 0.35}};
+  int best = 0;
+  double best_cost = 0;
+  for (int i = 0; i < 5; ++i) {
+    const int64_t tiles = (int64_t)((r.max_rows + shapes[i].bm - 1) / shapes[i].bm) * p->n_req * (n / shapes[i].bn);
+    const double cost = (double)((tiles + p->n_cu - 1) / p->n_cu) * shapes[i].cost;
+    if (i == 0 || cost < 0.98 * best_cost) {
+      best = i;
+      best_cost = cost;
+    }
+  }
+  switch (best) {
+    case 0: return launch_gemm_tiles<256, 256, 4, 2, 1, 2>(a, s);
+    case 1: return launch_gemm_tiles<256, 128, 4, 2, 1, 3>(a, s);
+    case 2: return launch_gemm_tiles<128, 128, 4, 2, 1, 4>(a, s);
+    case 3: return launch_gemm_tiles<128, 64, 2, 2, 2, 3>(a, s);
+    default: return launch_gemm_tiles<64, 64, 1, 1, 4, 2>(a, s);
+  }
 }
 
 hipError_t launch_rmsnorm_rows(const sx_plan* p, const RowsArg& r, const void* x, int x_tok, const void* gamma,
