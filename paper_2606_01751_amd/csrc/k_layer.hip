@@ -307,22 +307,33 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
 }
 
 // ---------------------------------------------------------------------------------------------
-// RMSNorm of listed rows: one wave per row, float32 sum of squares in a fixed order.
+// RMSNorm of listed rows: one workgroup per row, the row read once into registers (NC 16-byte pieces
+// per thread; longer rows read their further pieces again), float32 sum of squares in a fixed order
+// (thread, wave, waves in order).  Bound by HBM, for few rows by the latency of one read: 394 rows of
+// 4096 5.1 us, 6750 rows 21.5 us; one wave per row reading it twice took 9.2 and 28.5.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const ReqDev* __restrict__ reqs, const int32_t* __restrict__ rows,
                                                            const int32_t* __restrict__ n_rows, int max_rows,
                                                            const uint16_t* __restrict__ x, int x_tok,
                                                            const uint16_t* __restrict__ gamma, float eps, int H,
                                                            uint16_t* __restrict__ y, int y_tok) {
+  constexpr int NC = 2, STEP = 256 * 8;
+  __shared__ float part[4];
   const ReqDev rq = reqs[blockIdx.y];
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x;
   if (n >= n_rows[blockIdx.y] || n >= max_rows) return;
   const uint16_t* xr = x + row_index(rq, rows, n, x_tok) * H;
   uint16_t* yr = y + row_index(rq, rows, n, y_tok) * H;
+  const int c0 = threadIdx.x * 8;
+  uint4 xv[NC], gv[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = c0 + i * STEP;
+    xv[i] = c < H ? *(const uint4*)(xr + c) : make_uint4(0, 0, 0, 0);
+    gv[i] = c < H ? *(const uint4*)(gamma + c) : make_uint4(0, 0, 0, 0);
+  }
   float ss = 0.f;
-  for (int c = lane * 8; c < H; c += 64 * 8) {
-    const uint4 v = *(const uint4*)(xr + c);
+  auto add = [&](const uint4& v) {
     const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -330,27 +341,38 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const ReqDev* __restr
       ss = __builtin_fmaf(lo, lo, ss);
       ss = __builtin_fmaf(hi, hi, ss);
     }
-  }
+  };
+#pragma unroll
+  for (int i = 0; i < NC; ++i) add(xv[i]);
+  for (int c = c0 + NC * STEP; c < H; c += STEP) add(*(const uint4*)(xr + c));
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  ss = part[0] + part[1] + part[2] + part[3];
   const float inv = 1.0f / sqrtf(ss / (float)H + eps);
-  for (int c = lane * 8; c < H; c += 64 * 8) {
-    const uint4 v = *(const uint4*)(xr + c);
-    const uint4 gv = *(const uint4*)(gamma + c);
-    const uint32_t u[4] = {v.x, v.y, v.z, v.w}, gw[4] = {gv.x, gv.y, gv.z, gv.w};
+  auto put = [&](int c, const uint4& v, const uint4& g) {
+    const uint32_t u[4] = {v.x, v.y, v.z, v.w}, gw[4] = {g.x, g.y, g.z, g.w};
     uint32_t o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       o[i] = pack_bf16x2(bf16_lo(u[i]) * inv * bf16_lo(gw[i]), bf16_hi(u[i]) * inv * bf16_hi(gw[i]));
     *(uint4*)(yr + c) = make_uint4(o[0], o[1], o[2], o[3]);
-  }
+  };
+#pragma unroll
+  for (int i = 0; i < NC; ++i)
+    if (c0 + i * STEP < H) put(c0 + i * STEP, xv[i], gv[i]);
+  for (int c = c0 + NC * STEP; c < H; c += STEP) put(c, *(const uint4*)(xr + c), *(const uint4*)(gamma + c));
 }
 
 // ---------------------------------------------------------------------------------------------
-// RoPE of the fresh query and key rows of listed tokens, in place.  A thread owns 8 rotation
-// pairs of one token: it forms their cos / sin once (angle and cos / sin in float64, rounded to
-// float32) and rotates those pairs in every query and key head (float32, no contraction, bf16
-// store with round to nearest even).
+// RoPE of the fresh query and key rows of listed tokens, in place.  A workgroup takes 256 / (D / 2)
+// listed tokens: each thread forms the cos / sin of one (token, pair) (angle and cos / sin in float64,
+// rounded to float32) into LDS, then the threads share the tokens' query and key heads in units of 8
+// pairs (float32, no contraction, bf16 store with round to nearest even), consecutive threads on
+// consecutive bytes.  Bound by the float64 cos / sin latency for few rows, by HBM for many: 394 rows of
+// 32/8/128 7.7 us, 6750 rows 25 us; one thread per (token, 8 pairs) walking all heads took 27 and 42
+// (13 workgroups at 394 rows, each thread's 16 float64 cos / sin one after the other).
 // ---------------------------------------------------------------------------------------------
 template <int D, bool NEOX>
 __global__ __launch_bounds__(256) void rope_rows_kernel(const ReqDev* __restrict__ reqs, const int32_t* __restrict__ rows,
@@ -358,27 +380,38 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(const ReqDev* __restrict
                                                         const int32_t* __restrict__ tok_pos,
                                                         const double* __restrict__ theta, uint16_t* __restrict__ q,
                                                         uint16_t* __restrict__ k, int Hq, int Hkv) {
-  constexpr int UPR = D / 16;   // threads per token: 8 pairs each
+  constexpr int TB = 256 / (D / 2);   // tokens per workgroup
+  constexpr int UPH = D / 16;         // units of 8 pairs per head
+  __shared__ __attribute__((aligned(16))) float cs[TB][D / 2], sn[TB][D / 2];
   const ReqDev rq = reqs[blockIdx.y];
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = g / UPR;
-  const int u = g - n * UPR;
-  if (n >= n_rows[blockIdx.y] || n >= max_rows) return;
-  const int64_t t = row_index(rq, rows, n, true);
-  const double pos = (double)tok_pos[t];
-  float c[8], s[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const double phi = pos * theta[u * 8 + e];
-    c[e] = (float)cos(phi);
-    s[e] = (float)sin(phi);
+  const int n0 = blockIdx.x * TB;
+  const int nt = min(TB, min(n_rows[blockIdx.y], max_rows) - n0);   // tokens of this workgroup
+  if (nt <= 0) return;
+  {
+    const int tb = threadIdx.x / (D / 2), p = threadIdx.x % (D / 2);
+    const double phi = (double)tok_pos[row_index(rq, rows, n0 + min(tb, nt - 1), true)] * theta[p];
+    cs[tb][p] = (float)cos(phi);
+    sn[tb][p] = (float)sin(phi);
   }
-  // pair p = 8u + e: NEOX (p, p + D/2); GPT-J (2p, 2p + 1)
-  auto rotate_head = [&](uint16_t* h) {
+  __syncthreads();
+  const int per_tok = (Hq + Hkv) * UPH;
+  for (int x = threadIdx.x; x < nt * per_tok; x += 256) {
 #pragma clang fp contract(off)
+    const int tb = x / per_tok;
+    const int hu = x - tb * per_tok;
+    const int h = hu / UPH, u = hu % UPH;
+    const int64_t t = row_index(rq, rows, n0 + tb, true);
+    uint16_t* row = h < Hq ? q + (t * Hq + h) * D : k + (t * Hkv + h - Hq) * D;
+    float c[8], s[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      c[e] = cs[tb][u * 8 + e];
+      s[e] = sn[tb][u * 8 + e];
+    }
+    // pair p = 8u + e: NEOX (p, p + D/2); GPT-J (2p, 2p + 1)
     if constexpr (NEOX) {
-      uint4* pa = (uint4*)(h + u * 8);
-      uint4* pb = (uint4*)(h + D / 2 + u * 8);
+      uint4* pa = (uint4*)(row + u * 8);
+      uint4* pb = (uint4*)(row + D / 2 + u * 8);
       const uint4 va = *pa, vb = *pb;
       const uint32_t wa[4] = {va.x, va.y, va.z, va.w}, wb[4] = {vb.x, vb.y, vb.z, vb.w};
       uint32_t oa[4], ob[4];
@@ -392,7 +425,7 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(const ReqDev* __restrict
       *pa = make_uint4(oa[0], oa[1], oa[2], oa[3]);
       *pb = make_uint4(ob[0], ob[1], ob[2], ob[3]);
     } else {
-      uint4* pp = (uint4*)(h + u * 16);
+      uint4* pp = (uint4*)(row + u * 16);
       const uint4 v0 = pp[0], v1 = pp[1];
       const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
       uint32_t o[8];
@@ -404,9 +437,7 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(const ReqDev* __restrict
       pp[0] = make_uint4(o[0], o[1], o[2], o[3]);
       pp[1] = make_uint4(o[4], o[5], o[6], o[7]);
     }
-  };
-  for (int h = 0; h < Hq; ++h) rotate_head(q + (t * Hq + h) * D);
-  for (int h = 0; h < Hkv; ++h) rotate_head(k + (t * Hkv + h) * D);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -473,7 +504,7 @@ hipError_t launch_gemm_rows(const sx_plan* p, const RowsArg& r, const void* x, i
   a.x_tok = x_tok;
   a.y_tok = y_tok;
   // The tile whose rounds over the compute units take least: a workgroup per compute unit, and one
-  // 64-wide piece of k costs a round about 1.5 us on 256 x 256 tiles, 0.86 on 256 x 128, 0.60 on
+  // 64-wide piece of k costs a round about 1.5 us on 256 x 256 tiles, 0.95 on 256 x 128, 0.60 on
   // 128 x 128, 0.46 on 128 x 64 and 0.35 on 64 x 64 (measured, K = 4096, weights from HBM; bound by the
   // LDS reads and transfers between barriers on all but the largest).  So wide products keep the large
   // tile and few rows take the one that gives every compute unit a tile: the rows' count at which two
@@ -483,7 +514,7 @@ hipError_t launch_gemm_rows(const sx_plan* p, const RowsArg& r, const void* x, i
     int bn, bm;
     double cost;
   };
-  static const Shape shapes[] = {{256, 256, 1.5}, {256, 128, 0.86}, {128, 128, 0.60}, {128, 64, 0.46}, {64, 64, 0.35}};
+  static const Shape shapes[] = {{256, 256, 1.5}, {256, 128, 0.95}, {128, 128, 0.60}, {128, 64, 0.46}, {64, 64, 0.35}};
   int best = 0;
   double best_cost = 0;
   for (int i = 0; i < 5; ++i) {
@@ -505,7 +536,7 @@ hipError_t launch_gemm_rows(const sx_plan* p, const RowsArg& r, const void* x, i
 
 hipError_t launch_rmsnorm_rows(const sx_plan* p, const RowsArg& r, const void* x, int x_tok, const void* gamma,
                                float eps, int h, void* y, int y_tok, hipStream_t s) {
-  const dim3 grid((unsigned)((r.max_rows + 3) / 4), (unsigned)p->n_req);
+  const dim3 grid((unsigned)r.max_rows, (unsigned)p->n_req);
   hipLaunchKernelGGL(rmsnorm_rows_kernel, grid, dim3(256), 0, s, p->d_req, r.rows, r.n_rows, r.max_rows, (const uint16_t*)x, x_tok,
                      (const uint16_t*)gamma, eps, h, (uint16_t*)y, y_tok);
   return hipGetLastError();
@@ -513,8 +544,8 @@ hipError_t launch_rmsnorm_rows(const sx_plan* p, const RowsArg& r, const void* x
 
 hipError_t launch_rope_rows(const sx_plan* p, const RowsArg& r, void* q, void* k, hipStream_t s) {
   const int D = p->desc.head_dim;
-  const int64_t threads = (int64_t)r.max_rows * (D / 16);
-  const dim3 grid((unsigned)((threads + 255) / 256), (unsigned)p->n_req);
+  const int tb = 256 / (D / 2);   // tokens per workgroup
+  const dim3 grid((unsigned)((r.max_rows + tb - 1) / tb), (unsigned)p->n_req);
   const bool neox = p->desc.rope_style == SX_ROPE_NEOX;
   const int Hq = p->desc.n_q_heads, Hkv = p->desc.n_kv_heads;
 #define SX_ROPE(D_, N_)                                                                                               \
