@@ -336,7 +336,7 @@ sx_status sx_gemm_rows_split(const sx_plan* plan, const int32_t* rows, const int
                              const int32_t* part_n, void* const* y_parts, int32_t y_by_token, void* stream);
 
 /* RMSNorm: y[row] = x[row] / sqrt(mean_j x[row][j]^2 + eps) * gamma, rows of h elements
- * (h a multiple of 8), gamma [h]; the sum of squares is float32 in a fixed order. */
+ * (h a multiple of 8), gamma [h]; formed in float64 in a fixed order and rounded once. */
 sx_status sx_rmsnorm_rows(const sx_plan* plan, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
                           const void* x, int32_t x_by_token, const void* gamma, float eps, int32_t h, void* y,
                           int32_t y_by_token, void* stream);

@@ -308,9 +308,11 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
 
 // ---------------------------------------------------------------------------------------------
 // RMSNorm of listed rows: one workgroup per row, the row read once into registers (NC 16-byte pieces
-// per thread; longer rows read their further pieces again), float32 sum of squares in a fixed order
-// (thread, wave, waves in order).  Bound by HBM, for few rows by the latency of one read: 394 rows of
-// 4096 5.1 us, 6750 rows 21.5 us; one wave per row reading it twice took 9.2 and 28.5.
+// per thread; longer rows read their further pieces again), sum of squares in a fixed order (thread,
+// wave, waves in order).  Sum and products in float64, which hides under the row's transfers and leaves
+// one rounding, to bf16 by way of float32: a float32 product near a rounding boundary of bf16 is off by
+// a whole unit for every later reader of the row.  Bound by HBM, for few rows by the latency of one read: 394 rows of
+// 4096 5.3 us, 6750 rows 23 us; one wave per row reading it twice took 9.2 and 28.5.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const ReqDev* __restrict__ reqs, const int32_t* __restrict__ rows,
                                                            const int32_t* __restrict__ n_rows, int max_rows,
@@ -318,7 +320,7 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const ReqDev* __restr
                                                            const uint16_t* __restrict__ gamma, float eps, int H,
                                                            uint16_t* __restrict__ y, int y_tok) {
   constexpr int NC = 2, STEP = 256 * 8;
-  __shared__ float part[4];
+  __shared__ double part[4];
   const ReqDev rq = reqs[blockIdx.y];
   const int n = blockIdx.x;
   if (n >= n_rows[blockIdx.y] || n >= max_rows) return;
@@ -332,14 +334,14 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const ReqDev* __restr
     xv[i] = c < H ? *(const uint4*)(xr + c) : make_uint4(0, 0, 0, 0);
     gv[i] = c < H ? *(const uint4*)(gamma + c) : make_uint4(0, 0, 0, 0);
   }
-  float ss = 0.f;
+  double ss = 0.0;
   auto add = [&](const uint4& v) {
     const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float lo = bf16_lo(u[i]), hi = bf16_hi(u[i]);
-      ss = __builtin_fmaf(lo, lo, ss);
-      ss = __builtin_fmaf(hi, hi, ss);
+      const double lo = bf16_lo(u[i]), hi = bf16_hi(u[i]);
+      ss = __builtin_fma(lo, lo, ss);
+      ss = __builtin_fma(hi, hi, ss);
     }
   };
 #pragma unroll
@@ -350,13 +352,14 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const ReqDev* __restr
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
   __syncthreads();
   ss = part[0] + part[1] + part[2] + part[3];
-  const float inv = 1.0f / sqrtf(ss / (float)H + eps);
+  const double inv = 1.0 / sqrt(ss / (double)H + (double)eps);
   auto put = [&](int c, const uint4& v, const uint4& g) {
     const uint32_t u[4] = {v.x, v.y, v.z, v.w}, gw[4] = {g.x, g.y, g.z, g.w};
     uint32_t o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      o[i] = pack_bf16x2(bf16_lo(u[i]) * inv * bf16_lo(gw[i]), bf16_hi(u[i]) * inv * bf16_hi(gw[i]));
+      o[i] = pack_bf16x2((float)((double)bf16_lo(u[i]) * inv * (double)bf16_lo(gw[i])),
+                         (float)((double)bf16_hi(u[i]) * inv * (double)bf16_hi(gw[i])));
     *(uint4*)(yr + c) = make_uint4(o[0], o[1], o[2], o[3]);
   };
 #pragma unroll
