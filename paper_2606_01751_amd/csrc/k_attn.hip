@@ -1366,6 +1366,7 @@ hipError_t launch_attn_paged(const AttnLaunch& a, hipStream_t s) {
   if (a.dtype == SX_F32) return launch_attn_f32(a, true, s);
   const bool pv = a.out != nullptr;
   if (pv && a.lse != nullptr) return hipErrorInvalidValue;
+  if (attn_short_fits(a)) return launch_attn_short(a, true, s);
   if (a.D == 128) return pv ? launch_mfma<128, true, true>(a, s) : launch_mfma<128, true, false>(a, s);
   return pv ? launch_mfma<64, true, true>(a, s) : launch_mfma<64, true, false>(a, s);
 }
@@ -1383,6 +1384,7 @@ hipError_t launch_tile_order(const sx_plan* p, const int32_t* rows, const int32_
 
 hipError_t launch_attn_dense(const AttnLaunch& a, hipStream_t s) {
   if (a.dtype == SX_F32) return launch_attn_f32(a, false, s);
+  if (attn_short_fits(a)) return launch_attn_short(a, false, s);
   if (a.D == 128) return launch_mfma<128, false, true>(a, s);
   return launch_mfma<64, false, true>(a, s);
 }

@@ -11,6 +11,8 @@
 // Operand order: an MFMA multiplies one value of d per lane group, and the order in which the d
 // products are summed is free as long as both operands use it.  Group g of NG takes d = 4 NG j + 4 g + i
 // at step (j, i), so every operand row is read in 16-byte pieces.
+#include <algorithm>
+
 #include "sx_device.h"
 #include "sx_internal.h"
 
@@ -18,6 +20,9 @@ namespace sx {
 namespace {
 
 constexpr int FW = 8;     // waves per workgroup
+// Grid: x = KV head fastest, then kTilesX tiles; y = further tiles; z = request.  With the KV head
+// fastest the round-robin dispatch over the 8 XCDs keeps a head's K and V in one L2 (8 heads) or a few.
+constexpr int kTilesX = 64;
 constexpr int kWideTiles = 256;   // 32-column tiles from which the attention uses them (one per compute unit)
 
 struct AttnF {
@@ -94,7 +99,8 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
   const int lc = lane % CT, g = lane / CT;
   // key of the piece that a lane's value x is
   auto key_in = [&](int x) { return (CT == 32 ? 8 : 16) * (x >> 2) + 4 * g + (x & 3); };
-  const int kvh = blockIdx.y;
+  const int kvh = blockIdx.x % a.Hkv;
+  const int tile = (int)(blockIdx.y * kTilesX + blockIdx.x / a.Hkv);
   const int r = blockIdx.z;
   int tok_off, bt_off = 0, nrows;
   if constexpr (PAGED) {
@@ -108,8 +114,8 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
   }
   const int ncols = nrows * a.G;
   const int ntiles = (ncols + CT - 1) / CT;
-  if ((int)blockIdx.x >= ntiles) return;
-  const int c0 = (ntiles - 1 - (int)blockIdx.x) * CT;   // the tiles with the most keys first
+  if (tile >= ntiles) return;
+  const int c0 = (ntiles - 1 - tile) * CT;   // the tiles with the most keys first
   auto row_of = [&](int c) { return min(c, ncols - 1) / a.G; };
   auto pos_of = [&](int n) -> int { return PAGED ? a.rows[tok_off + n] : n; };
   const int my_row = row_of(c0 + lc);
@@ -358,9 +364,10 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
   __shared__ double s_sum[FW][CT];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lc = lane % CT, g = lane / CT;
-  const int kvh = blockIdx.y;
+  const int kvh = blockIdx.x % a.Hkv;
+  const int tile = (int)(blockIdx.y * kTilesX + blockIdx.x / a.Hkv);
   const ReqDev rq = a.reqs[blockIdx.z];
-  const int j0 = (int)blockIdx.x * CT;   // first keys first: the most probe rows see them
+  const int j0 = tile * CT;   // first keys first: the most probe rows see them
   if (j0 >= rq.T) return;
   const int key = j0 + lc;
   f32x4_t kb[NJ];
@@ -443,6 +450,10 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
   }
 }
 
+dim3 grid_of(int64_t tiles, int Hkv, int n_req) {
+  return dim3((unsigned)(Hkv * std::min<int64_t>(tiles, kTilesX)), (unsigned)((tiles + kTilesX - 1) / kTilesX), (unsigned)n_req);
+}
+
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnLaunch& L, bool paged, hipStream_t s) {
@@ -468,7 +479,7 @@ hipError_t launch_attn_f32(const AttnLaunch& L, bool paged, hipStream_t s) {
   // 600 78 / 66, 4096 497 / 401 us
   const bool wide = ((int64_t)L.grid_rows * a.G + 31) / 32 * L.Hkv * L.n_req >= kWideTiles;
   const int ct = wide ? 32 : 16;
-  const dim3 grid((unsigned)(((int64_t)L.grid_rows * a.G + ct - 1) / ct), (unsigned)L.Hkv, (unsigned)L.n_req);
+  const dim3 grid = grid_of(((int64_t)L.grid_rows * a.G + ct - 1) / ct, L.Hkv, L.n_req);
   const bool pv = L.out != nullptr;
 #define SX_F32_LAUNCH(D_, P_, V_)                                                                           \
   do {                                                                                                      \
@@ -505,7 +516,7 @@ hipError_t launch_colsum_f32(const sx_plan* p, double* colsum, const void* q, co
   // the tile width as for the attention above (512 tokens, 8/2/64: 16 / 32 keys 11.3 / 14.1 us)
   const bool wide = ((int64_t)p->max_T + 31) / 32 * a.Hkv * p->n_req >= kWideTiles;
   const int ct = wide ? 32 : 16;
-  const dim3 grid((unsigned)((p->max_T + ct - 1) / ct), (unsigned)a.Hkv, (unsigned)p->n_req);
+  const dim3 grid = grid_of((p->max_T + ct - 1) / ct, a.Hkv, p->n_req);
 #define SX_F32_COLSUM(D_)                                                                                \
   do {                                                                                                   \
     if (wide) hipLaunchKernelGGL((colsum_f32_kernel<D_, 32>), grid, dim3(FW * 64), 0, s, a);            \

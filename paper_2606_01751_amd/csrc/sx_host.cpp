@@ -676,6 +676,7 @@ sx_status sx_sparseq_score(const sx_plan* p, const void* q, const void* k_cache,
   a.D = p->desc.head_dim;
   a.n_req = p->n_req;
   a.grid_rows = p->max_probe;
+  a.max_keys = p->max_T;
   a.dtype = p->desc.dtype;
   a.scale = p->scale;
   a.q = q;
@@ -795,6 +796,7 @@ sx_status sx_sparse_attn(const sx_plan* p, const void* q, const int32_t* rows, c
   a.D = p->desc.head_dim;
   a.n_req = p->n_req;
   a.grid_rows = max_rows;
+  a.max_keys = p->max_T;
   a.dtype = p->desc.dtype;
   a.scale = p->scale;
   a.q = q;
@@ -858,6 +860,7 @@ sx_status sx_full_attn(const sx_layer_desc* desc, const void* q, const void* k, 
   a.D = desc->head_dim;
   a.n_req = n_requests;
   a.grid_rows = max_seqlen;
+  a.max_keys = max_seqlen;
   a.dtype = desc->dtype;
   a.scale = effective_scale(desc);
   a.q = q;

@@ -172,6 +172,7 @@ hipError_t launch_silu_mul_rows(const sx_plan* p, const RowsArg& r, const void* 
 // Attention family.  Mode selects the query rows and the key source.
 struct AttnLaunch {
   int Hq, Hkv, D, n_req, grid_rows;   // grid_rows: max query rows of any request
+  int max_keys;                       // max tokens of any request
   int dtype;
   float scale;
   const void* q;
@@ -209,6 +210,9 @@ constexpr int kDenseQueueStride = 256;
 constexpr int kLseSplit = 4;   // most key pieces per row tile of the log-sum-exp pass
 hipError_t launch_attn_paged(const AttnLaunch& a, hipStream_t s);   // rows over a paged cache
 hipError_t launch_attn_dense(const AttnLaunch& a, hipStream_t s);   // all rows, dense K/V
+// few query rows (bfloat16): 32-column workgroups that split the keys over their waves
+bool attn_short_fits(const AttnLaunch& a);
+hipError_t launch_attn_short(const AttnLaunch& a, bool paged, hipStream_t s);
 // column sums of the Sparse-Q probabilities; lse: base-2 sums indexed by probe (lse_tok = 0, the
 // plan's pass-1 scratch) or natural-log sums indexed by token (lse_tok = 1, a caller's input)
 hipError_t launch_colsum(const sx_plan* p, const ScoreScratch& sc, const void* q, const void* kc, const float* lse,
