@@ -81,6 +81,10 @@ KERNELS = {
     "attn_mfma_kernel<128, true, true, true>": ("sx_sparse_attn", "k_attn.hip", True),
     "attn_mfma_kernel<128, false, true, true>": ("sx_full_attn", "k_attn.hip", True),
     "attn_mfma_kernel<128, false, true, false>": ("sx_full_attn", "k_attn.hip", True),   # (under graph capture)
+    # few query rows
+    "attn_short_kernel<128, true, true>": ("sx_sparse_attn", "k_attn_short.hip", True),
+    "attn_short_kernel<128, false, true>": ("sx_full_attn", "k_attn_short.hip", True),
+    "attn_short_kernel<128, true, false>": ("sx_sparseq_score", "k_attn_short.hip", False),
     # two-pass scoring only (layers without a preceding full layer)
     "attn_mfma_kernel<128, true, false, false>": ("sx_sparseq_score", "k_attn.hip", False),
     "lse_merge_kernel": ("sx_sparseq_score", "k_attn.hip", False),
@@ -92,9 +96,9 @@ KERNELS = {
     "scatter_kernel": ("sx_kv_scatter", "k_copy.hip", True),
     "realign_scatter_kernel": ("sx_realign_scatter_masked", "k_copy.hip", True),   # (also the row-list variants)
     "mark_rows_kernel": ("sx_realign_scatter", "k_copy.hip", False),   # (also sx_realign_scatter_layers)
-    "fill_u8_kernel": ("sx_rows_mask", "k_copy.hip", True),
+    "rows_mask_kernel": ("sx_rows_mask", "k_attn.hip", True),
+    "fill_u8_kernel": ("sx_rows_mask", "k_copy.hip", False),   # (beyond 16384 rows)
     "mask_rows_kernel": ("sx_rows_mask", "k_copy.hip", False),
-    "tile_order_kernel": ("sx_rows_mask", "k_attn.hip", False),
     "topk_hist_kernel": ("sx_topk_select", "k_topk.hip", False),
     "topk_bound_kernel": ("sx_topk_select", "k_topk.hip", False),
     "topk_write_kernel": ("sx_topk_select", "k_topk.hip", True),

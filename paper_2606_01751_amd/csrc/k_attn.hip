@@ -69,7 +69,7 @@ struct AttnK {
   // g_dense_queue)
   int32_t* queue;
   int qslot;
-  // sparse attention: planned order of the queue items (tile_order_kernel; NULL or out[0] != the
+  // sparse attention: planned order of the queue items (plan_tile_order; NULL or out[0] != the
   // item count: the queue's own order)
   const int32_t* order;
 };
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(512, 1) void attn_mfma_kernel(AttnK ka) {
   // (sparse, and full attention outside graph capture) runs a persistent grid instead: about one
   // workgroup per compute unit and KV head, each taking its head's next item from that head's
   // queue whenever it finishes one.  The items then go to whichever compute unit frees first
-  // (greedy longest-first, or the planned order of tile_order_kernel), with no gap for the
+  // (greedy longest-first, or the planned order of plan_tile_order), with no gap for the
   // hardware to dispatch another workgroup; the hardware's own dispatch hands the workgroups of an
   // XCD to its shader engines in turn and holds the rest back while the next one's engine is full,
   // which left a tenth of the compute units idle in the tail.  A workgroup whose head's queue is
@@ -746,8 +746,8 @@ __global__ __launch_bounds__(512, 1) void attn_mfma_kernel(AttnK ka) {
 // bin capacity for which first-fit-decreasing packs the tiles into m bins, m being the
 // workgroups per head, found by a parallel search over candidate capacities), the m largest tiles
 // opening the bins, and lists the tiles by their planned start, so that the workgroups, each
-// taking the next tile when it finishes one, follow the plan.  One workgroup of 1024 threads; out[0] = number of tiles n, out[1 + k] = the
-// queue item taken k-th; out[0] = -1 (the queue's order) when n > 8 m or m > 64.
+// taking the next tile when it finishes one, follow the plan.  Run by one workgroup of 1024 threads;
+// out[0] = number of tiles n, out[1 + k] = the queue item taken k-th; out[0] = -1 (the queue's order) when n > 8 m or m > 64.
 // Every item index of [0, n) appears exactly once, whatever the costs.
 constexpr int kOrderCost0 = 4;
 
@@ -764,18 +764,18 @@ __device__ __forceinline__ int rank_of(const uint32_t* key, int n, int i) {
   return r;
 }
 
-__global__ __launch_bounds__(1024) void tile_order_kernel(const ReqDev* __restrict__ reqs,
-                                                          const int32_t* __restrict__ rows,
-                                                          const int32_t* __restrict__ n_rows, int max_rows,
-                                                          int n_req, int rpw, int m, int32_t* __restrict__ out) {
+__device__ void plan_tile_order(const ReqDev* __restrict__ reqs, const int32_t* __restrict__ rows,
+                                const int32_t* __restrict__ n_rows, int max_rows, int n_req, int rpw, int m,
+                                int32_t* __restrict__ out) {
   constexpr int NMAX = kOrderMax;   // items planned: at most 8 per bin, at most 64 bins
   static_assert(NMAX == 8 * 64, "eight items per bin, 64 bins");
   __shared__ __attribute__((aligned(16))) uint32_t key[NMAX];
   __shared__ int32_t item[NMAX];   // queue item of the k-th largest cost
   __shared__ int32_t cost[NMAX];   // its cost
-  __shared__ uint32_t plan[16][NMAX];   // each wave's packing: planned start << 6 | bin per item
+  constexpr int NC = 8;             // capacities (waves) per round of the search
+  __shared__ uint32_t plan[NC][NMAX];   // each wave's packing: planned start << 6 | bin per item
   __shared__ int s_n, s_sum, s_max, s_lo, s_hi, s_hi0, s_best, s_fail;
-  __shared__ int s_ok[16];
+  __shared__ int s_ok[NC];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (tid == 0) {
     int n = 0;
@@ -831,39 +831,47 @@ __global__ __launch_bounds__(1024) void tile_order_kernel(const ReqDev* __restri
   // largest items opening one bin each (so they start together, as longest-first would start them:
   // their workgroups stream the same keys through the L2 at the same time; letting first fit pack
   // two of them into one bin made the plan 1 % shorter but tripled the sparse attention's L2
-  // misses); returns whether every item fitted.  With rec, the i-th item's planned start << 6 | bin.
-  auto ffd = [&](int C, bool rec) -> bool {
-    // branch-free per item (a branch per step made the pass several times slower); lanes past
-    // the bins hold a load no item fits on
-    int load = lane < m ? 0 : 0x3FFFFFFF;
-    bool ok = true;
+  // misses); returns whether every item fitted, and leaves each item's planned start << 6 | bin in this
+  // wave's row of `plan`.
+  auto ffd = [&](int C) -> bool {
+    // no branch per item, the packing kept in lane registers (item 64 k + l in lane l).  Lanes past the bins
+    // hold a load that no item fits on; an item that fits nowhere goes to lane 63, found out at the end.
+    constexpr int kFull = 0x3FFFFFFF;
+    int load = lane < m ? creg[0] : kFull;
 #pragma unroll
     for (int k = 0; k < NMAX / 64; ++k) {
       const int jn = min(64, n - 64 * k);
-      for (int j = 0; j < jn; ++j) {
-        const int c = __builtin_amdgcn_readlane(creg[k], j);
-        const int cand = load + c;
-        const uint64_t fits = 64 * k + j < m ? 1ull << (64 * k + j) : __ballot(cand <= C);
-        ok = ok && fits != 0;
-        const int b = fits ? (int)__builtin_ctzll(fits) : 64;
-        if (rec) plan[wv][64 * k + j] = ((uint32_t)__builtin_amdgcn_readlane(load, b & 63) << 6) | (uint32_t)b;
+      int rec = lane;   // (the m largest: bin = item, start 0)
+#pragma unroll 2
+      for (int j = k == 0 ? m : 0; j < jn; ++j) {
+        const int cand = load + __builtin_amdgcn_readlane(creg[k], j);
+        const int b = (int)__builtin_ctzll(__ballot(cand <= C) | 1ull << 63);
+        const int start = __builtin_amdgcn_readlane(load, b);
+        rec = lane == j ? (start << 6) | b : rec;
         load = lane == b ? cand : load;
       }
+      if (lane < jn) plan[wv][64 * k + lane] = (uint32_t)rec;
     }
-    return ok;
+    return __ballot(lane < m ? load > C : load != kFull) == 0;
   };
-  // parallel search: every wave packs at one capacity of (lo, hi] and keeps its packing; the
-  // interval shrinks 16-fold per round, down to a step of 1/256 of the capacity.  If no capacity up
-  // to the first guess fits, the search goes on up to the bound where first fit always fits.
-  while (!s_fail && (s_hi - s_lo > max(1, s_hi >> 8) || s_best < 0)) {
+  // parallel search: every wave packs at one capacity and keeps its packing, the smallest that fits is
+  // taken.  The first round tries the lower bound and 7 steps of 1/256 above it, where a packing mostly
+  // exists; failing that, 8 capacities of (lo, hi] per round, the interval shrinking 8-fold down to a step of
+  // 1/256, up to the bound where first fit always fits.  Bound by the instructions of a pass, which the
+  // waves of a SIMD share: 106 tiles 16 us, 45 with 16 capacities in three rounds and 20 instructions
+  // per item.
+  bool first = true;
+  while (!s_fail && (first || s_hi - s_lo > max(1, s_hi >> 8) || s_best < 0)) {
     const int lo = s_lo, hi = s_hi;
-    const int C = lo + (int)(((int64_t)(hi - lo) * (wv + 1) + 15) / 16);
-    const bool ok = ffd(C, true);
-    if (lane == 0) s_ok[wv] = ok ? C : -C;
+    const int C = first ? lo + 1 + max(1, lo >> 8) * wv : lo + (int)(((int64_t)(hi - lo) * (wv + 1) + NC - 1) / NC);
+    if (wv < NC) {
+      const bool ok = ffd(C);
+      if (lane == 0) s_ok[wv] = ok ? C : -C;
+    }
     __syncthreads();
     if (tid == 0) {
-      int nlo = lo, nhi = hi, best = -1;
-      for (int w = 0; w < 16; ++w) {
+      int nlo = lo, nhi = first ? 0x7fffffff : hi, best = -1;
+      for (int w = 0; w < NC; ++w) {
         if (s_ok[w] > 0) {
           if (s_ok[w] <= nhi) {
             nhi = s_ok[w];
@@ -873,15 +881,19 @@ __global__ __launch_bounds__(1024) void tile_order_kernel(const ReqDev* __restri
           nlo = max(nlo, -s_ok[w]);
         }
       }
-      if (best < 0) {   // nothing fitted up to hi (its packing failed too): search above it
+      if (first) {
+        if (best >= 0) nlo = nhi;   // (done)
+        else nhi = max(hi, nlo + 1);
+      } else if (best < 0) {   // nothing fitted up to hi (its packing failed too): search above it
         if (hi >= s_hi0) s_fail = 1;   // (cannot happen: first fit always fits at s_hi0)
         nlo = hi;
-        nhi = s_hi0;
+        nhi = max(hi, s_hi0);
       }
       s_lo = nlo;
       s_hi = nhi;
       s_best = best;
     }
+    first = false;
     __syncthreads();
   }
   if (s_fail) {
@@ -895,6 +907,58 @@ __global__ __launch_bounds__(1024) void tile_order_kernel(const ReqDev* __restri
   __syncthreads();
   for (int i = tid; i < n; i += blockDim.x) out[1 + rank_of(key, n, i)] = item[i];
   if (tid == 0) out[0] = n;
+}
+
+// Byte mask of a row list, and in the same launch (first workgroup, when `order` is given) the planned tile
+// order: neither waits for the other.  A mask workgroup owns kMaskTokens tokens of one request: it marks
+// them in LDS from the whole row list (a few loads per thread, whatever the list's order) and writes them
+// once, so no clearing pass is needed.
+constexpr int kMaskTokens = 8192;
+__global__ __launch_bounds__(1024) void rows_mask_kernel(const ReqDev* __restrict__ reqs, const int32_t* __restrict__ rows,
+                                                         const int32_t* __restrict__ n_rows, int max_rows, int n_req,
+                                                         int rpw, int m, int32_t* __restrict__ order,
+                                                         uint8_t* __restrict__ mask) {
+  __shared__ __attribute__((aligned(16))) uint8_t mark[kMaskTokens];
+  int chunk = blockIdx.x;
+  if (order) {
+    if (chunk == 0) {
+      if (blockIdx.y == 0) plan_tile_order(reqs, rows, n_rows, max_rows, n_req, rpw, m, order);
+      return;
+    }
+    --chunk;
+  }
+  const ReqDev rq = reqs[blockIdx.y];
+  const int t0 = chunk * kMaskTokens;
+  if (t0 >= rq.T) return;
+  const int tid = threadIdx.x;
+  constexpr int PT = kMaskTokens / 1024;   // bytes per thread
+  static_assert(PT == 8, "a thread clears and writes 8 bytes");
+  const int n = min(n_rows[blockIdx.y], max_rows);
+  const int32_t* list = rows + rq.tok_off;
+  const int len = min(kMaskTokens, rq.T - t0);
+  // batches of independent loads, the first in flight while the marks are cleared
+  constexpr int NB = 16;
+  int v[NB];
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int q = 0; q < NB; ++q) v[q] = i0 + q * 1024 + tid < n ? list[i0 + q * 1024 + tid] - t0 : -1;
+  };
+  load(0);
+  *(uint2*)(mark + tid * PT) = make_uint2(0, 0);
+  __syncthreads();
+  for (int i0 = 0; i0 < n; i0 += NB * 1024) {
+    if (i0) load(i0);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (v[q] >= 0 && v[q] < len) mark[v[q]] = 1;
+  }
+  __syncthreads();
+  uint8_t* dst = mask + rq.tok_off + t0;
+  if (tid * PT + PT <= len && ((uintptr_t)(dst + tid * PT) & 7) == 0) {
+    *(uint2*)(dst + tid * PT) = *(const uint2*)(mark + tid * PT);
+  } else {
+    for (int i = tid * PT; i < min(len, tid * PT + PT); ++i) dst[i] = mark[i];
+  }
 }
 
 // Log-sum-exp of the pieces of the split log-sum-exp pass, for one (probe row, query head) per
@@ -1371,14 +1435,24 @@ hipError_t launch_attn_paged(const AttnLaunch& a, hipStream_t s) {
   return pv ? launch_mfma<64, true, true>(a, s) : launch_mfma<64, true, false>(a, s);
 }
 
-hipError_t launch_tile_order(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
-                             hipStream_t s) {
+hipError_t launch_rows_mask(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
+                            uint8_t* mask, hipStream_t s) {
+  const bool order = p->desc.dtype == SX_BF16;
+  // every mask workgroup walks the whole list: up to 16384 rows (one batch of loads per thread) that costs
+  // less than a clearing launch and one that marks, beyond it those two take the mask (whole selection with
+  // its mask, three launches / one for the mask: 16000 tokens 58 / 33 us, 28600 rows 25.7 / 29.7)
+  const bool one = max_rows <= 16384;
+  if (!one) {
+    const hipError_t e = launch_rows_mask_two(p, rows, n_rows, max_rows, mask, s);
+    if (e != hipSuccess || !order) return e;
+  }
   const int G = p->desc.n_q_heads / p->desc.n_kv_heads;
   const int rpw = COLS / G;
   const int64_t items = (int64_t)(max_rows + rpw - 1) / rpw * p->n_req;   // as the attention launch bounds them
   const int m = (int)std::min<int64_t>(items, std::max(1, p->n_cu / p->desc.n_kv_heads));
-  hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(1024), 0, s, p->d_req, rows, n_rows, max_rows, p->n_req, rpw,
-                     std::max(m, 1), p->d_order);
+  const unsigned chunks = one ? (unsigned)((p->max_T + kMaskTokens - 1) / kMaskTokens) : 0u;
+  hipLaunchKernelGGL(rows_mask_kernel, dim3(chunks + (order ? 1 : 0), one ? (unsigned)p->n_req : 1u), dim3(1024), 0, s,
+                     p->d_req, rows, n_rows, max_rows, p->n_req, rpw, std::max(m, 1), order ? p->d_order : nullptr, mask);
   return hipGetLastError();
 }
 

@@ -357,8 +357,8 @@ hipError_t realign_scatter_dispatch(const sx_plan* p, int32_t n_layers, const sx
   return hipSuccess;
 }
 
-hipError_t launch_rows_mask(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
-                            uint8_t* mask, hipStream_t s) {
+hipError_t launch_rows_mask_two(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
+                                uint8_t* mask, hipStream_t s) {
   hipLaunchKernelGGL(fill_u8_kernel, dim3((unsigned)((p->total + 255) / 256)), dim3(256), 0, s, mask, p->total,
                      (uint8_t)0);
   hipError_t e = hipGetLastError();

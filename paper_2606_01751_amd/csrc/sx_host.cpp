@@ -531,10 +531,7 @@ sx_status sx_rows_mask(const sx_plan* p, const int32_t* rows, const int32_t* n_r
   }
   sx_status st = check_launch(sx::launch_rows_mask(p, rows, n_rows, max_rows, mask, (hipStream_t)stream),
                               "sx_rows_mask launch");
-  if (st != SX_OK || p->desc.dtype != SX_BF16) return st;
-  // the planned row-tile order of sx_sparse_attn for this row list
-  st = check_launch(sx::launch_tile_order(p, rows, n_rows, max_rows, (hipStream_t)stream), "sx_rows_mask order launch");
-  if (st == SX_OK) {
+  if (st == SX_OK && p->desc.dtype == SX_BF16) {   // (the launch has planned sx_sparse_attn's order for this row list)
     p->order_rows = rows;
     p->order_n_rows = n_rows;
     p->order_max_rows = max_rows;

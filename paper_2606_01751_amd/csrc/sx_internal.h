@@ -135,9 +135,13 @@ hipError_t launch_probe_pad_clear(const sx_plan* p, const ScoreScratch& sc, hipS
 hipError_t launch_realign_scatter(const sx_plan* p, int32_t n_layers, const sx_layer_kv* layers, const int32_t* rows,
                                   const int32_t* n_rows, int32_t max_rows, uint32_t gen, bool clear_marks,
                                   const uint8_t* sel, hipStream_t s);
-// mask[off_r + t] = 1 for every listed row t, 0 for every other token of the plan
+// mask[off_r + t] = 1 for every listed row t, 0 for every other token of the plan; bfloat16 plans: also the
+// planned order of sparse attention's row tiles for the row list (plan->d_order)
 hipError_t launch_rows_mask(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
                             uint8_t* mask, hipStream_t s);
+// the mask alone, in a clearing and a marking launch
+hipError_t launch_rows_mask_two(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
+                                uint8_t* mask, hipStream_t s);
 hipError_t launch_topk(const sx_plan* p, const float* scores, double ratio, int32_t* rows, int32_t* n_rows,
                        hipStream_t s);
 
@@ -201,9 +205,6 @@ struct AttnLaunch {
   const int32_t* order;   // sparse attention: the plan's planned tile order, or NULL
 };
 constexpr int kOrderMax = 512;   // most row tiles the tile order is planned for (8 per workgroup, 64 workgroups)
-// planned order of sparse attention's row tiles for the row list (plan->d_order)
-hipError_t launch_tile_order(const sx_plan* p, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
-                             hipStream_t s);
 // queue slots of persistent full attention on one device, and counters per slot (KV heads + 1)
 constexpr int kDenseQueueSlots = 64;
 constexpr int kDenseQueueStride = 256;
