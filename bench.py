@@ -89,7 +89,6 @@ KERNELS = {
     "attn_mfma_kernel<128, true, false, false>": ("sx_sparseq_score", "k_attn.hip", False),
     "lse_merge_kernel": ("sx_sparseq_score", "k_attn.hip", False),
     "colsum_kernel<128, 2>": ("sx_sparseq_score", "k_attn.hip", True),
-    "colsum_kernel<128, 1>": ("sx_sparseq_score", "k_attn.hip", True),
     "probe_gather_kernel<128>": ("sx_sparseq_score", "k_attn.hip", False),
     "head_reduce_kernel": ("sx_sparseq_score", "k_copy.hip", False),
     "realign_kernel": ("sx_rope_realign", "k_copy.hip", True),

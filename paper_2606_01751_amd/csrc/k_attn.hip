@@ -989,7 +989,8 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const ReqDev* __restrict
   lse[(int64_t)(rq.tok_off + i) * Hq + h] = lse_base2 ? lse2 : lse2 * 0.69314718055994531f;
 }
 
-constexpr int CS_WAVE_KEYS = 32;   // keys per key tile of a column-sum wave
+constexpr int CS_WAVE_KEYS = 32;   // keys of a column-sum wave
+static_assert(8 * CS_WAVE_KEYS == kColsumKeys, "the host counts the key tiles");
 
 // Gather of the Sparse-Q probe columns for colsum_kernel: the query rows of every probe row
 // and the base-2 log-sum-exp of every (probe row, query head), in probe order and grouped by KV
@@ -1024,17 +1025,22 @@ __global__ __launch_bounds__(256) void probe_gather_kernel(const uint16_t* __res
   }
 }
 
-// Sparse-Q column sums from the gathered probe columns, key-stationary: a workgroup owns
-// 8 x 32 x NKT keys of one KV head (a wave's NKT tiles of 32 keys held in registers as the MFMA B
-// operand) and computes S = Q K^T, p = 2^(scale*log2e*s - lse2) masked causally, summed per key.
+// Sparse-Q column sums from the gathered probe columns, key-stationary: a workgroup owns 8 x 32 keys of
+// one KV head (a wave's 32 keys held in registers as the MFMA B operand) and one of `split` shares of the
+// probe columns, and computes S = Q K^T, p = 2^(scale*log2e*s - lse2) masked causally, summed per key.
 // In this orientation a lane's accumulator elements all belong to one key (its lane) and 16 probe
-// columns, so a key's sum is a per-lane sum: one fp32 partial per key tile, flushed every chunk
-// into an fp64 total.  Each query-operand read from LDS feeds NKT MFMAs.  The probe columns (probe
-// row x query head of the group) stream in chunks of RC probe rows x G heads (at most 64 columns,
-// two 32-column MFMA groups) that move global -> LDS directly: the query rows (16 bytes per lane,
-// XOR-swizzled 16-byte chunks), the chunk's 64 log-sum-exps and 64 probe positions (one per column
-// slot, 4 bytes per lane), triple-buffered and issued two chunks ahead.  No global load in the loop
-// feeds an address, so the loop waits only for transfers issued two chunks earlier.
+// columns, so a key's sum is a per-lane sum: one fp32 partial, flushed every chunk into an fp64 total
+// (the shares are added with the KV heads).  The probe columns (probe row x query head of the group)
+// stream in chunks of RC probe rows x G heads (at most 64 columns, two 32-column MFMA groups) that move
+// global -> LDS directly: the query rows (16 bytes per lane, XOR-swizzled 16-byte chunks), the chunk's
+// 64 log-sum-exps and 64 probe positions (one per column slot, 4 bytes per lane), triple-buffered and
+// issued two chunks ahead.  No global load in the loop feeds an address, so the loop waits only for
+// transfers issued two chunks earlier.
+// Bound by the exponentials beside the MFMAs (one each per pair, 1.55 x slower beside the other wave's
+// MFMAs) and, for few tiles, by the longest workgroup.  128 registers and 50 KB of LDS let two workgroups
+// share a compute unit, each covering the other's barriers: that beats two key tiles per wave (half the
+// probe-column reads, 228 registers, one workgroup), 361 -> 307 us at 32768 tokens with 2048 probe rows
+// and 1926 -> 1724 us for eight requests of 120000 tokens; with the shares 171 -> 115 us at 8192 tokens.
 struct ColsumK {
   const uint16_t* k;
   const uint16_t* qp;
@@ -1042,16 +1048,18 @@ struct ColsumK {
   const ReqDev* reqs;
   const int32_t* bt;
   const int32_t* probe;
-  double* colsum;
+  double* colsum;   // [Hkv][split][sum T]
   int64_t total, n_probe_total;
   int Hq, Hkv, G, RC, n_req;
+  int split;        // workgroups that share a key tile's probe columns
   float scale_log2;
 };
 
-template <int D, int NKT>
-__global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
+// WGS: workgroups per compute unit that the registers have to allow (8 waves each, two per SIMD).
+template <int D, int WGS>
+__global__ __launch_bounds__(512, 2 * WGS) void colsum_kernel(ColsumK a) {
   constexpr int NW = 8;
-  constexpr int KEYS = NW * CS_WAVE_KEYS * NKT;   // keys per workgroup
+  constexpr int KEYS = NW * CS_WAVE_KEYS;   // keys per workgroup
   constexpr int ROWB = D * 2;                 // bytes of one query row (one column)
   constexpr int NCH = ROWB / 16;              // 16-byte chunks per column
   constexpr int CPP = 1024 / ROWB;            // columns per 1 KB transfer
@@ -1076,40 +1084,38 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
   // stream the same request's probe columns
   int r, kt;
   locate_request((int)(blockIdx.x / (unsigned)a.Hkv), a.n_req,
-                 [&](int rr) { return (a.reqs[rr].T + KEYS - 1) / KEYS; }, &r, &kt, lane);
+                 [&](int rr) { return (a.reqs[rr].T + KEYS - 1) / KEYS * a.split; }, &r, &kt, lane);
   if (r < 0) return;
   r = __builtin_amdgcn_readfirstlane(r);
   kt = __builtin_amdgcn_readfirstlane(kt);
+  const int part = kt % a.split;   // this workgroup's share of the tile's chunks
+  kt /= a.split;
   const ReqDev rq = a.reqs[r];
   const int T = rq.T;
   const int j0 = kt * KEYS;
-  const int jw = j0 + w * (CS_WAVE_KEYS * NKT);   // the wave's first key
+  const int jw = j0 + w * CS_WAVE_KEYS;   // the wave's first key
   const int G = a.G;
   const int RC = a.RC;
   const int ncol = RC * G;                    // columns of a full chunk (<= 64)
-  // B operand of key tile t: lane (l32, hg) holds dims 16 s + 8 hg .. + 7 of key jw + 32 t + l32
-  bf16x8_t kb[NKT][D / 16];
+  // B operand: lane (l32, hg) holds dims 16 s + 8 hg .. + 7 of key jw + l32
+  bf16x8_t kb[D / 16];
+  const int key = jw + l32;
+  const uint16_t* kp = nullptr;
+  if (key < T) {
+    const int32_t blk = a.bt[rq.bt_off + (key >> 4)];
+    kp = a.k + (((int64_t)blk * a.Hkv + kvh) * 16 + (key & 15)) * D + hg * 8;
+  }
 #pragma unroll
-  for (int t = 0; t < NKT; ++t) {
-    const int key = jw + CS_WAVE_KEYS * t + l32;
-    const uint16_t* kp = nullptr;
-    if (key < T) {
-      const int32_t blk = a.bt[rq.bt_off + (key >> 4)];
-      kp = a.k + (((int64_t)blk * a.Hkv + kvh) * 16 + (key & 15)) * D + hg * 8;
-    }
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) {
-      uint4 v = kp ? *(const uint4*)(kp + 16 * s) : make_uint4(0, 0, 0, 0);
-      kb[t][s] = __builtin_bit_cast(bf16x8_t, v);
-    }
+  for (int s = 0; s < D / 16; ++s) {
+    uint4 v = kp ? *(const uint4*)(kp + 16 * s) : make_uint4(0, 0, 0, 0);
+    kb[s] = __builtin_bit_cast(bf16x8_t, v);
   }
   const int32_t* probe = a.probe + rq.tok_off;
-  const int np = rq.n_probe;
-  int lo = 0, hi = np;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (probe[mid] < j0) lo = mid + 1; else hi = mid;
-  }
+  // probe rows [lo, np): those that see a key of the tile, in whole chunks split evenly
+  int lo = __builtin_amdgcn_readfirstlane(lower_bound_wave(probe, rq.n_probe, j0, lane));
+  const int share = ((rq.n_probe - lo + RC - 1) / RC + a.split - 1) / a.split * RC;
+  lo = min(lo + part * share, rq.n_probe);
+  const int np = min(lo + share, rq.n_probe);
   const int nchunk = (np - lo + RC - 1) / RC;
   // ---- transfers of chunk k into buffer k mod NBUF (this wave's share).  Rows past the request's
   // probe rows read the padding (at most RC - 1 < kProbePad rows), so no clamping.  A chunk's query
@@ -1198,22 +1204,13 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
   // Chunks whose first probe row lies before the workgroup's last key may miss keys (causal mask),
   // and the last chunk may hold fewer than RC probe rows; both take the checked path.  Probe rows
   // ascend, so the masked chunks come first: nmask of them.
-  int hm = lo, hx = np;
-  while (hm < hx) {
-    const int mid = (hm + hx) >> 1;
-    if (probe[mid] < j0 + KEYS - 1) hm = mid + 1; else hx = mid;
-  }
+  const int hm = lo + __builtin_amdgcn_readfirstlane(lower_bound_wave(probe + lo, np - lo, j0 + KEYS - 1, lane));
   const int nmask = min(nchunk, (hm - lo + RC - 1) / RC);
   const bool last_partial = (np - lo) % RC != 0;
   const int nfast = last_partial ? nchunk - 1 : nchunk;   // chunks [nmask, nfast) take the fast path
 
-  double acc64[NKT];
-  float acc32[NKT];
-#pragma unroll
-  for (int t = 0; t < NKT; ++t) {
-    acc64[t] = 0.0;
-    acc32[t] = 0.f;
-  }
+  double acc64 = 0.0;
+  float acc32 = 0.f;
   // K must be in registers before the first transfer wait (the compiler does not count the
   // transfers, so a later wait of its own for K would also wait for them)
   SX_WAIT_VMCNT(0);
@@ -1233,13 +1230,9 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
   auto lds16 = [](uint32_t addr) -> bf16x8_t {
     return *(const __attribute__((address_space(3))) bf16x8_t*)(uintptr_t)addr;
   };
-  // S of the chunk in the buffer at Cb against the NKT key tiles, column group gi in s[gi]: lane
-  // (l32, hg), element e holds column 32 gi + 8 (e / 4) + 4 hg + e % 4 of the chunk and key
-  // jw + 32 t + l32
-  struct SG {
-    f32x16_t s[NKT];
-  };
-  SG sg[2];
+  // S of the chunk in the buffer at Cb, column group gi in sg[gi]: lane (l32, hg), element e holds
+  // column 32 gi + 8 (e / 4) + 4 hg + e % 4 of the chunk and key jw + l32
+  f32x16_t sg[2];
   auto matrix_phase = [&](int j) {
     if (j >= nchunk) return;
     uint32_t Cb = (uint32_t)__builtin_amdgcn_readfirstlane((int)(smem_lds + (uint32_t)((j % NBUF) * CHB)));
@@ -1247,8 +1240,7 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
     __builtin_amdgcn_s_setprio(2);
 #pragma unroll
     for (int gi = 0; gi < 2; ++gi)
-#pragma unroll
-      for (int t = 0; t < NKT; ++t) sg[gi].s[t] = f32x16_t{};
+      sg[gi] = f32x16_t{};
 #pragma unroll
     for (int st = 0; st < D / 16; ++st) {
       uint32_t qa_addr = Cb + q_off[st];
@@ -1256,12 +1248,10 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
 #pragma unroll
       for (int gi = 0; gi < 2; ++gi) {
         const bf16x8_t qa = lds16(qa_addr + (uint32_t)(gi * 32 * ROWB));
-#pragma unroll
-        for (int t = 0; t < NKT; ++t)
-          sg[gi].s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kb[t][st], sg[gi].s[t], 0, 0, 0);
+        sg[gi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kb[st], sg[gi], 0, 0, 0);
       }
     }
-    sched_pipelined<2 * NKT * (D / 16), 1, 4>();
+    sched_pipelined<2 * (D / 16), 1, 4>();
     __builtin_amdgcn_s_setprio(0);
   };
   // sums of chunk j.  Fast path: every column valid, no mask.  Checked path: column c counts for
@@ -1295,32 +1285,22 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
           pos[4 * q + 2] = c0 + 2 < nvalid ? v.z : -1;
           pos[4 * q + 3] = c0 + 3 < nvalid ? v.w : -1;
         }
+        float sum = acc32;
 #pragma unroll
-        for (int t = 0; t < NKT; ++t) {
-          const int key = jw + CS_WAVE_KEYS * t + l32;
-          float sum = acc32[t];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sg[gi].s[t][e], c2, -l2[e]));
-            sum += key <= pos[e] ? p : 0.f;
-          }
-          acc32[t] = sum;
+        for (int e = 0; e < 16; ++e) {
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sg[gi][e], c2, -l2[e]));
+          sum += key <= pos[e] ? p : 0.f;
         }
+        acc32 = sum;
       } else {
+        float sum = acc32;
 #pragma unroll
-        for (int t = 0; t < NKT; ++t) {
-          float sum = acc32[t];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(sg[gi].s[t][e], c2, -l2[e]));
-          acc32[t] = sum;
-        }
+        for (int e = 0; e < 16; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(sg[gi][e], c2, -l2[e]));
+        acc32 = sum;
       }
     }
-#pragma unroll
-    for (int t = 0; t < NKT; ++t) {
-      acc64[t] += (double)acc32[t];
-      acc32[t] = 0.f;
-    }
+    acc64 += (double)acc32;
+    acc32 = 0.f;
   };
   auto vphase = [&](int j) {
     if (j < 0 || j >= nchunk) return;
@@ -1354,12 +1334,8 @@ __global__ __launch_bounds__(512, 1) void colsum_kernel(ColsumK a) {
     }
   }
   // the two lane halves hold the same keys (different columns)
-#pragma unroll
-  for (int t = 0; t < NKT; ++t) {
-    const double tot = acc64[t] + __shfl_xor(acc64[t], 32, 64);
-    const int key = jw + CS_WAVE_KEYS * t + l32;
-    if (hg == 0 && key < T) a.colsum[(int64_t)kvh * a.total + rq.tok_off + key] = tot;
-  }
+  const double tot = acc64 + __shfl_xor(acc64, 32, 64);
+  if (hg == 0 && key < T) a.colsum[((int64_t)kvh * a.split + part) * a.total + rq.tok_off + key] = tot;
 }
 
 template <int D, bool PAGED, bool PV>
@@ -1498,19 +1474,11 @@ hipError_t launch_colsum(const sx_plan* p, const ScoreScratch& sc, const void* q
   c.G = G;
   c.RC = 64 / G;
   c.n_req = p->n_req;
+  c.split = p->cs_split;
   c.scale_log2 = p->scale * 1.4426950408889634f;
-  // two key tiles per wave (each staged query column feeds twice the MFMAs and the probe columns
-  // stream half as often) while that still leaves two workgroups per CU, else one
-  const int64_t wg2 = ((p->max_T + 511) / 512) * c.Hkv * p->n_req;
-  if (wg2 >= 512) {
-    const dim3 grid((unsigned)wg2);
-    if (D == 128) hipLaunchKernelGGL((colsum_kernel<128, 2>), grid, dim3(512), 0, s, c);
-    else hipLaunchKernelGGL((colsum_kernel<64, 2>), grid, dim3(512), 0, s, c);
-  } else {
-    const dim3 grid((unsigned)(((p->max_T + 255) / 256) * c.Hkv * p->n_req));
-    if (D == 128) hipLaunchKernelGGL((colsum_kernel<128, 1>), grid, dim3(512), 0, s, c);
-    else hipLaunchKernelGGL((colsum_kernel<64, 1>), grid, dim3(512), 0, s, c);
-  }
+  const dim3 grid((unsigned)(p->cs_tiles * c.Hkv * c.split));
+  if (D == 128) hipLaunchKernelGGL((colsum_kernel<128, 2>), grid, dim3(512), 0, s, c);
+  else hipLaunchKernelGGL((colsum_kernel<64, 2>), grid, dim3(512), 0, s, c);
   return hipGetLastError();
 }
 

@@ -273,13 +273,20 @@ __global__ __launch_bounds__(256) void realign_scatter_kernel(
   }
 }
 
-// scores[i] = sum over KV heads h (in order) of colsum[h][i], rounded once to float32.
-__global__ __launch_bounds__(256) void head_reduce_kernel(const double* __restrict__ colsum, int64_t total, int Hkv,
+// scores[i] = sum over the n parts h (KV heads and their shares, in order) of colsum[h][i], rounded once to
+// float32; 8 independent loads at a time.
+__global__ __launch_bounds__(256) void head_reduce_kernel(const double* __restrict__ colsum, int64_t total, int n,
                                                           float* __restrict__ scores) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
   double s = 0.0;
-  for (int h = 0; h < Hkv; ++h) s += colsum[(int64_t)h * total + i];
+  for (int h0 = 0; h0 < n; h0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = h0 + q < n ? colsum[(int64_t)(h0 + q) * total + i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += v[q];
+  }
   scores[i] = (float)s;
 }
 
@@ -403,7 +410,8 @@ hipError_t launch_realign_scatter(const sx_plan* p, int32_t n_layers, const sx_l
 
 hipError_t launch_head_reduce(const sx_plan* p, const double* colsum, float* scores, hipStream_t s) {
   const dim3 grid((unsigned)((p->total + 255) / 256));
-  hipLaunchKernelGGL(head_reduce_kernel, grid, dim3(256), 0, s, colsum, p->total, p->desc.n_kv_heads, scores);
+  hipLaunchKernelGGL(head_reduce_kernel, grid, dim3(256), 0, s, colsum, p->total,
+                     p->desc.n_kv_heads * p->cs_split, scores);
   return hipGetLastError();
 }
 

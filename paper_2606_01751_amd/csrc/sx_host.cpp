@@ -144,6 +144,41 @@ void free_plan(sx_plan* p) {
   delete p;
 }
 
+size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
+
+// Bytes of the three parts of the scoring scratch (sx_sparseq_score_static lays them out one after the
+// other) with the column sums in `split` shares.
+struct ScoreBytes {
+  size_t colsum, qp, lse;
+  size_t sum() const { return colsum + qp + lse; }
+};
+ScoreBytes score_bytes(const sx_plan* p, int split) {
+  const size_t Hq = (size_t)p->desc.n_q_heads, Hkv = (size_t)p->desc.n_kv_heads, rows = (size_t)p->n_probe + sx::kProbePad;
+  const bool bf16 = p->desc.dtype == SX_BF16;
+  return {align256(Hkv * (size_t)split * (size_t)p->total * sizeof(double)),
+          bf16 ? align256(rows * Hq * (size_t)p->desc.head_dim * sizeof(uint16_t)) : 0,
+          bf16 ? align256(rows * Hq * sizeof(float)) : 0};
+}
+constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
+constexpr int kColsumSplit = 8;   // most shares
+
+// Workgroups that share a key tile's probe columns.  The column sums of a key tile take as long as it has
+// probe chunks (64 columns each, the first tiles the most), two workgroups per compute unit; shares even
+// that out until there are about four rounds of workgroups, as long as a share keeps two chunks and the
+// scratch stays within the static entry point's where one share does (both entry points use the same
+// shares, so their scores are the same bits).  Measured (selecting layer, 1 share / chosen): 1000 tokens
+// of 32/8/128 52 / 36 us, 8192 273 / 228, 16000 600 / 540, 8192 of 8/2/64 193 / 86 us.
+int colsum_split(const sx_plan* p) {
+  if (p->desc.dtype != SX_BF16) return 1;
+  const int rc = 64 / (p->desc.n_q_heads / p->desc.n_kv_heads);
+  const int64_t chunks = (p->max_probe + rc - 1) / rc;
+  int split = 1;
+  while (split < kColsumSplit && p->cs_tiles * p->desc.n_kv_heads * split < 2048 && chunks / (2 * split) >= 2 &&
+         (score_bytes(p, 2 * split).sum() <= kStaticScratchBytes || score_bytes(p, 1).sum() > kStaticScratchBytes))
+    split *= 2;
+  return split;
+}
+
 // The scoring scratch a plan owns (allocated and padded in sx_plan_create).
 sx::ScoreScratch plan_scratch(const sx_plan* p) { return sx::ScoreScratch{p->d_colsum, p->d_qp, p->d_lse2p}; }
 
@@ -341,6 +376,8 @@ sx_status sx_plan_create(const sx_layer_desc* desc, const sx_request* requests, 
     off += T;
   }
   p->n_realign = (int64_t)ra.size();
+  for (const auto& h : p->reqs) p->cs_tiles += (h.T + sx::kColsumKeys - 1) / sx::kColsumKeys;
+  p->cs_split = colsum_split(p);
 
   st = SX_OK;
   if (st == SX_OK) st = dev_upload(p, &p->d_req, rdev);
@@ -359,7 +396,7 @@ sx_status sx_plan_create(const sx_layer_desc* desc, const sx_request* requests, 
   if (st == SX_OK) st = dev_upload(p, &p->d_queue, std::vector<int32_t>((size_t)desc->n_kv_heads + 1, 0));
   if (st == SX_OK) st = dev_upload(p, &p->d_order, std::vector<int32_t>(1 + (size_t)sx::kOrderMax, -1));
   if (st == SX_OK) st = dev_alloc(p, &p->d_lse, (size_t)total * desc->n_q_heads);
-  if (st == SX_OK) st = dev_alloc(p, &p->d_colsum, (size_t)total * desc->n_kv_heads);
+  if (st == SX_OK) st = dev_alloc(p, &p->d_colsum, (size_t)total * desc->n_kv_heads * p->cs_split);
   if (st == SX_OK) {
     // selection scratch, zeroed once: every call leaves the histograms at zero
     const int64_t chunks = (p->max_T + sx::kTopkChunk - 1) / sx::kTopkChunk;
@@ -707,7 +744,6 @@ namespace {
 // Scratch of sx_sparseq_score_static: one array per device, in the library's code object, so the
 // entry point needs no allocation.  Host code never uses the array's name as an address: the
 // device address comes from hipGetSymbolAddress, once per device on its first call.
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 __device__ __align__(256) char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -729,8 +765,6 @@ sx_status static_scratch(void** out) {
   return SX_OK;
 }
 
-size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
-
 }  // namespace
 
 extern "C" {
@@ -740,13 +774,9 @@ sx_status sx_sparseq_score_static(const sx_plan* p, const void* q, const void* k
   if (!p) return fail(SX_EINVAL, "plan is NULL");
   if (!q || !k_cache || !scores) return fail(SX_EINVAL, "NULL tensor argument");
   if (!lse_in) return fail(SX_EINVAL, "sx_sparseq_score_static needs lse_in (one-pass scoring)");
-  const int64_t Hq = p->desc.n_q_heads, Hkv = p->desc.n_kv_heads, G = Hq / Hkv;
   const bool bf16 = p->desc.dtype == SX_BF16;
-  const int64_t rows = p->n_probe + sx::kProbePad;
-  const size_t colsum_b = align256((size_t)(Hkv * p->total) * sizeof(double));
-  const size_t qp_b = bf16 ? align256((size_t)(rows * Hq * p->desc.head_dim) * sizeof(uint16_t)) : 0;
-  const size_t lse_b = bf16 ? align256((size_t)(Hkv * rows * G) * sizeof(float)) : 0;
-  const size_t need = colsum_b + qp_b + lse_b;
+  const ScoreBytes parts = score_bytes(p, p->cs_split);
+  const size_t need = parts.sum();
   if (need > kStaticScratchBytes)
     return fail(SX_EUNSUPPORTED, "the plan needs %zu bytes of scoring scratch; the static scratch holds %zu", need,
                 kStaticScratchBytes);
@@ -754,8 +784,8 @@ sx_status sx_sparseq_score_static(const sx_plan* p, const void* q, const void* k
   sx_status st = static_scratch(&base);
   if (st != SX_OK) return st;
   char* b = (char*)base;
-  const sx::ScoreScratch sc{(double*)b, bf16 ? (void*)(b + colsum_b) : nullptr,
-                            bf16 ? (float*)(b + colsum_b + qp_b) : nullptr};
+  const sx::ScoreScratch sc{(double*)b, bf16 ? (void*)(b + parts.colsum) : nullptr,
+                            bf16 ? (float*)(b + parts.colsum + parts.qp) : nullptr};
   hipStream_t s = (hipStream_t)stream;
   if (bf16) {
     // the gathered probe columns' padding rows (zero queries, +inf log-sum-exps): an earlier call may

@@ -13,6 +13,7 @@ namespace sx {
 
 constexpr int kBlock = 16;     // paged-cache block size supported by the kernels
 constexpr int kTail = 64;      // tail-fallback rows (Section 3.2)
+constexpr int kColsumKeys = 256;   // keys per tile (workgroup) of the bfloat16 column sums
 constexpr int kProbePad = 64;  // padding rows past the probe lists and gathered probe columns
 
 // Per-request device metadata.
@@ -90,7 +91,9 @@ struct sx_plan {
   uint32_t* d_rmark = nullptr;    // [sum T] row-set generation marks (sx_realign_scatter)
   mutable uint32_t rgen = 0;      // last generation used
   float* d_lse = nullptr;         // scratch [sum T][Hq]
-  double* d_colsum = nullptr;     // scratch [Hkv][sum T]
+  double* d_colsum = nullptr;     // scratch [Hkv][cs_split][sum T]
+  int64_t cs_tiles = 0;           // key tiles of the column sums, all requests
+  int32_t cs_split = 1;           // workgroups that share a key tile's probe columns in the column sums
   int32_t* d_tok_pos = nullptr;   // [sum T] RoPE position of every token in the new sequence
   double* d_theta = nullptr;      // [d/2] RoPE frequencies base^(-2i/d), float64
   void* d_qp = nullptr;           // scratch [Hkv][n_probe][Hq / Hkv][d]: query rows of the probe rows (bf16 plans)
@@ -115,7 +118,7 @@ hipError_t launch_realign(const sx_plan* p, const void* src_k, const void* src_v
                           hipStream_t s);
 hipError_t launch_scatter(const sx_plan* p, const void* k_new, const void* v_new, const int32_t* rows,
                           const int32_t* n_rows, int32_t max_rows, void* kc, void* vc, hipStream_t s);
-// Scratch of the Sparse-Q column sums: per-KV-head float64 sums [Hkv][sum T]; (bf16 plans) the
+// Scratch of the Sparse-Q column sums: per-KV-head float64 sums [Hkv][cs_split][sum T]; (bf16 plans) the
 // gathered probe columns, queries [Hkv][n_probe + kProbePad][Hq / Hkv][d] and base-2 log-sum-exps
 // [Hkv][n_probe + kProbePad][Hq / Hkv], whose kProbePad padding rows must hold zero queries and
 // +inf log-sum-exps (a column read there adds exp2(-inf) = 0).

@@ -1,0 +1,67 @@
+"""bfloat16 Sparse-Q scores with the probe columns of a key tile in 1 to 8 shares (GPU), against float64.
+
+Tolerance: a score sums probabilities 2^(s - lse) whose exponents are float32 sums of d products, off by at most
+d 2^-24 sum |q k| scale (2e-5 for N(0, 1) inputs at d = 128), the sums themselves in float64: 1e-4 of the value.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workloads as W
+from sxgpu import GpuLayer, host, log
+
+pytestmark = pytest.mark.gpu
+
+try:
+    import paper_2606_01751_amd as sx
+except Exception:  # pragma: no cover
+    sx = None
+
+# (q heads, kv heads, d, pieces per request): one share (few chunks), shares of two chunks, a last share
+# with a partial chunk or with none, tiles that no probe row but the last sees, G not dividing 64, and a
+# plan with enough tiles for fewer shares
+CASES = [
+    (8, 2, 128, [[(5, False), (40, True)]]),
+    (32, 8, 128, [[(33, False), (300, True), (31, False)]]),
+    (28, 4, 64, [[(200, True), (137, False), (300, True), (90, False)], [(20, False)]]),
+    (8, 8, 64, [[(300, True), (259, False), (300, True), (1, False)]]),
+    (64, 1, 64, [[(100, True), (37, False)]]),
+    (16, 2, 128, [[(64, False), (1500, True), (400, False)], [(257, True)], [(255, False), (2, True)]]),
+]
+
+
+@pytest.mark.parametrize("one_pass", [False, True], ids=["two-pass", "one-pass"])
+@pytest.mark.parametrize("hq,hkv,d,pieces", CASES, ids=[f"{c[0]}-{c[1]}-{c[2]}-{i}" for i, c in enumerate(CASES)])
+def test_scores(hq, hkv, d, pieces, one_pass):
+    log(f"[score shares] {hq}/{hkv}/{d} {pieces} {one_pass}")
+    w = W.custom_workload([[(n, c, 30 if c else 0, None) for n, c in p] for p in pieces], n_q_heads=hq, n_kv_heads=hkv,
+                          head_dim=d, dtype="bf16", rope_base=1e4, seed=hq + d)
+    t = W.layer_tensors(w, 0)
+    g = GpuLayer(w, t)
+    g.realign()
+    g.scatter_nonreused()
+    lse = None
+    kc = host(g.k_cache)
+    keys = [O.gather_tokens(req, w, kc).astype(np.float64) for req in w.requests]
+    scale = O.softmax_scale(d)
+    if one_pass:
+        full = np.zeros((w.total_tokens, hq), np.float32)
+        for req, off, k in zip(w.requests, w.token_offsets, keys):
+            for h in range(hq):
+                z = t["q"][off:off + req.n_tokens, h].astype(np.float64) @ k[:, h // (hq // hkv)].T * scale
+                z[np.triu_indices(req.n_tokens, 1)] = -np.inf
+                full[off:off + req.n_tokens, h] = np.logaddexp.reduce(z, 1)
+        lse = torch.from_numpy(full).cuda()
+    sx.sparseq_score(g.plan, g.t["q"], g.k_cache, g.scores, lse_in=lse)
+    torch.cuda.synchronize()
+    first = host(g.scores)
+    for r, (req, off, k) in enumerate(zip(w.requests, w.token_offsets, keys)):
+        ref = O.sparseq_scores(t["q"][off:off + req.n_tokens], k, O.probe_positions(req.n_tokens, req.segments), scale)
+        assert (np.abs(first[off:off + req.n_tokens] - ref) <= 1e-4 * np.abs(ref) + 1e-7).all(), r
+    sx.sparseq_score(g.plan, g.t["q"], g.k_cache, g.scores, lse_in=lse)
+    again = host(g.scores)
+    assert np.array_equal(again, first)
+    if one_pass:
+        sx.sparseq_score_static(g.plan, g.t["q"], g.k_cache, g.scores, lse)
+        assert np.array_equal(host(g.scores), first)
