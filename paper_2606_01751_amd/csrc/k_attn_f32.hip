@@ -49,11 +49,16 @@ __device__ __forceinline__ void wave_sync() {
 
 __device__ __forceinline__ f32x4_t ld4(const float* p) { return *(const f32x4_t*)p; }
 
-// e^x for x <= 0, -inf included: v_exp_f32 (1 ulp) of x log2 e with the constant in two parts, so that
-// the result is within 2 ulp + 2^-24 |x| of e^x, as the score x itself is known; a third of expf's
-// instructions.  (Below 2^-126 it is 0.)
+// e^x for x <= 0, -inf included: v_exp_f32 (1 ulp) of y = x log2 e rounded, and what the rounding and
+// the constant's own leave out, r, by 2^r = 1 + r ln 2: within 2 ulp of e^x, in half of expf's
+// instructions.  Without r the error is 2^-24 |x|, which the 512-token layer's scores showed (7.9e-8
+// against 6.5e-8 with expf).  r is kept finite where y is not: 2^y is 0 (or NaN) there.  (Below 2^-126
+// the result is 0.)
 __device__ __forceinline__ float exp_neg(float x) {
-  return __builtin_amdgcn_exp2f(__builtin_fmaf(x, 1.44269502f, x * 1.92596299e-8f));
+  const float y = x * 1.44269502f;
+  const float r = __builtin_fmaf(x, 1.92596299e-8f, __builtin_fmaf(x, 1.44269502f, -y));
+  const float e = __builtin_amdgcn_exp2f(y);
+  return __builtin_fmaf(e, fminf(fmaxf(r, -1.f), 1.f) * 0.693147181f, e);
 }
 
 // CT x CT tiles of v_mfma_f32: NG lane groups hold one value of the contraction each, a lane owns
