@@ -98,6 +98,8 @@ KERNELS = {
     "rows_mask_kernel": ("sx_rows_mask", "k_attn.hip", True),
     "fill_u8_kernel": ("sx_rows_mask", "k_copy.hip", False),   # (beyond 16384 rows)
     "mask_rows_kernel": ("sx_rows_mask", "k_copy.hip", False),
+    "topk_one_kernel<1>": ("sx_topk_select", "k_topk.hip", True),   # (requests up to 8192 tokens)
+    "topk_one_kernel<2>": ("sx_topk_select", "k_topk.hip", True),   # (up to 16384)
     "topk_hist_kernel": ("sx_topk_select", "k_topk.hip", False),
     "topk_bound_kernel": ("sx_topk_select", "k_topk.hip", False),
     "topk_write_kernel": ("sx_topk_select", "k_topk.hip", True),

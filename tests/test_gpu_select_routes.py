@@ -48,8 +48,9 @@ SCORES = {
     "signed": lambda rng, n: rng.normal(0, 1, n) * 10.0 ** rng.integers(-30, 30, n),
     "near": lambda rng, n: (np.float32(1.5).view(np.uint32) + rng.integers(0, 300, n).astype(np.uint32)).view(np.float32),
 }
-# request lengths at the edges of a thread's 8 tokens, a 2048-token chunk and a mask workgroup's 8192 tokens
-LENGTHS = [(1, 7, 8, 9), (2047, 2049), (8191, 8193, 16384), (32768,), (32767, 5), (32769, 100)]
+# request lengths at the edges of a thread's 8 tokens, a 2048-token chunk, the one-workgroup selection's rounds of
+# 8192 tokens and its limit of two, and a mask workgroup's 8192 tokens
+LENGTHS = [(1, 7, 8, 9), (2047, 2049), (8192, 777), (8191, 8193, 16384), (16385, 9), (32768,), (32767, 5), (32769, 100)]
 
 
 @pytest.mark.parametrize("kind", SCORES)
