@@ -223,9 +223,10 @@ sx_status sx_realign_scatter_layers(const sx_plan* plan, int32_t n_layers, const
  * (rows[off_r .. off_r + min(n_rows[r], max_rows))), 0 for every other token of the plan.
  * mask is caller-owned DEVICE memory of sum T bytes; rows/n_rows/max_rows as in sx_kv_scatter.
  * Listed values outside [0, T_r) are ignored.  No host sync.  bfloat16 plans: the same launch
- * plans, in the plan's scratch, the order in which sx_sparse_attn takes its row tiles (Multifit over their estimated costs); sx_sparse_attn uses it when called with the
- * same rows, n_rows and max_rows, as the sparse layers that share R are (Section 3.4).  The order
- * changes only which workgroup computes a row tile, never a result. */
+ * plans, in the plan's scratch, the order in which sx_sparse_attn takes its row tiles (Multifit
+ * over their estimated costs); sx_sparse_attn uses it when called with the same rows, n_rows and
+ * max_rows, as the sparse layers that share R are (Section 3.4).  The order changes only which
+ * workgroup computes a row tile, never a result. */
 sx_status sx_rows_mask(const sx_plan* plan, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
                        uint8_t* mask, void* stream);
 

@@ -1397,7 +1397,7 @@ hipError_t launch_mfma(const AttnLaunch& L, hipStream_t s) {
 
 }  // namespace
 
-// float32 variants (vector ALU), defined in k_attn_f32.hip
+// float32 variants, defined in k_attn_f32.hip
 hipError_t launch_attn_f32(const AttnLaunch& a, bool paged, hipStream_t s);
 hipError_t launch_colsum_f32(const sx_plan* p, double* colsum, const void* q, const void* kc, const float* lse,
                              int lse_tok, hipStream_t s);
