@@ -11,6 +11,12 @@
 // Operand order: an MFMA multiplies one value of d per lane group, and the order in which the d
 // products are summed is free as long as both operands use it.  Group g of NG takes d = 4 NG j + 4 g + i
 // at step (j, i), so every operand row is read in 16-byte pieces.
+//
+// The tile width is chosen by the size of the launch, so it must not show in a result: a request gives the
+// same bits in any batch.  An MFMA adds its products to the accumulator one after the other in group order, so
+// two of a 32-wide tile (two products each) taken in the order of one of a 16-wide tile (four) form the same
+// sum; what a lane of a 32-wide tile sums on the vector ALU it keeps in two parts, those of the two lanes that
+// share the work on a 16-wide tile (Tile::PH), added in the 16-wide tile's order.
 #include <algorithm>
 
 #include "sx_device.h"
@@ -66,6 +72,7 @@ __device__ __forceinline__ float exp_neg(float x) {
 template <int CT>
 struct Tile {
   static constexpr int NG = 64 / CT, AE = CT * CT / 64;
+  static constexpr int PH = 4 / NG;   // parts (MFMAs) of a lane for one 16-wide tile's lane group (MFMA)
   typedef float acc_t __attribute__((ext_vector_type(AE)));
   static __device__ __forceinline__ acc_t mfma(float x, float y, acc_t c) {
     if constexpr (CT == 32) return __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
@@ -89,7 +96,7 @@ struct Tile {
 // 103 TFLOP/s (29 ms).
 template <int D, int CT, bool PAGED, bool PV>
 __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
-  constexpr int NG = Tile<CT>::NG, AE = Tile<CT>::AE;
+  constexpr int NG = Tile<CT>::NG, AE = Tile<CT>::AE, PH = Tile<CT>::PH;
   constexpr int KT = 32 / CT;               // key tiles per piece
   constexpr int KPP = KT * AE;              // keys per lane and piece
   constexpr int QS = D + 4;                 // floats per Q row in LDS
@@ -158,7 +165,9 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
       for (int j = 0; j < NJ; ++j) kr[b][j] = ld4(p + 4 * NG * j);
     }
   };
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l[PH];
+#pragma unroll
+  for (int h = 0; h < PH; ++h) l[h] = 0.f;
   acc_t o[PV ? VW : 1];
 #pragma unroll
   for (int j = 0; j < (PV ? VW : 1); ++j) o[j] = acc_t{};
@@ -198,12 +207,16 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
 #pragma unroll
     for (int b = 0; b < KT; ++b) s[b] = acc_t{};
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const f32x4_t qj = ld4(qs + lc * QS + 4 * NG * j + 4 * g);
+    for (int j = 0; j < NJ; j += PH) {
+      f32x4_t qj[PH];
+#pragma unroll
+      for (int h = 0; h < PH; ++h) qj[h] = ld4(qs + lc * QS + 4 * NG * (j + h) + 4 * g);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int b = 0; b < KT; ++b) s[b] = Tile<CT>::mfma(kr[b][j][i], qj[i], s[b]);
+        for (int h = 0; h < PH; ++h)
+#pragma unroll
+          for (int b = 0; b < KT; ++b) s[b] = Tile<CT>::mfma(kr[b][j + h][i], qj[h][i], s[b]);
     }
     if (PRE && t + FW < np) load_k(t + FW, bn);
     float p[KPP];
@@ -218,7 +231,8 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
     const float mn = fmaxf(m, mx);
     if (__ballot(mn > m)) {
       const float f = mn == -INFINITY ? 1.f : exp_neg(m - mn);
-      l *= f;
+#pragma unroll
+      for (int h = 0; h < PH; ++h) l[h] *= f;
       if constexpr (PV) {
 #pragma unroll
         for (int j = 0; j < VW; ++j)
@@ -231,7 +245,7 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
 #pragma unroll
     for (int x = 0; x < KPP; ++x) {
       p[x] = exp_neg(p[x] - msub);
-      l += p[x];
+      l[(x >> 2) % PH] += p[x];   // (keys 16 b + 8 h + 4 g ..: part h)
     }
     if constexpr (PV) {
       // A masked key must not reach a column even when its V is infinite or NaN (0 x inf): on pieces
@@ -248,9 +262,15 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
           }
       }
 #pragma unroll
-      for (int x = 0; x < KPP; ++x)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int j = 0; j < VW; ++j) o[j] = Tile<CT>::mfma(vr[x][j], p[x], o[j]);
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int h = 0; h < PH; ++h) {
+            const int x = (b * PH + h) * 4 + i;
+#pragma unroll
+            for (int j = 0; j < VW; ++j) o[j] = Tile<CT>::mfma(vr[x][j], p[x], o[j]);
+          }
       if (__ballot(odd)) {
         // rare: key by key, the probabilities through this wave's part of the merge buffer
         static_assert(FW / 2 * RS / FW >= 32 * CT, "a wave's part of the merge buffer holds a piece");
@@ -278,10 +298,12 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
     bo[1] = bn[1];
   }
 #pragma unroll
-  for (int i = CT; i < 64; i <<= 1) l += __shfl_xor(l, i, 64);
+  for (int h = 0; h < PH; ++h)
+#pragma unroll
+    for (int i = CT; i < 64; i <<= 1) l[h] += __shfl_xor(l[h], i, 64);
   if (g == 0) {
     ms[w][lc] = m;
-    ls[w][lc] = l;
+    ls[w][lc] = PH == 1 ? l[0] : l[0] + l[PH - 1];
   }
   __syncthreads();
   float M = -INFINITY, L = 0.f;
@@ -360,7 +382,7 @@ struct ColsumF {
 
 template <int D, int CT>
 __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
-  constexpr int NG = Tile<CT>::NG, AE = Tile<CT>::AE;
+  constexpr int NG = Tile<CT>::NG, AE = Tile<CT>::AE, PH = Tile<CT>::PH;
   constexpr int KT = 32 / CT;               // column tiles per piece
   constexpr int NJ = D / (4 * NG);          // 16-byte operand pieces per lane and row
   typedef typename Tile<CT>::acc_t acc_t;
@@ -384,7 +406,8 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
     for (int j = 0; j < NJ; ++j) kb[j] = ld4(kp + 4 * NG * j);
   }
   const int32_t* probe = a.probe + rq.tok_off;
-  const int lo = lower_bound_wave(probe, rq.n_probe, j0, lane);   // first probe row that sees a key of the tile
+  // first probe row that sees a key of the 32 (the pieces start there at either tile width)
+  const int lo = lower_bound_wave(probe, rq.n_probe, j0 & ~31, lane);
   const int ncols = (rq.n_probe - lo) * a.G;
   // piece t: the query rows of this lane's columns, and the log-sum-exp and position of column lane % 32
   // (position -1 past the end)
@@ -408,7 +431,9 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
     ql = a.lse[(int64_t)(rq.tok_off + (a.lse_tok ? cp : lo + n)) * a.Hq + kvh * a.G + cc - n * a.G];
     qp = c < ncols ? cp : -1;
   };
-  double acc = 0.0;
+  double acc[PH];
+#pragma unroll
+  for (int h = 0; h < PH; ++h) acc[h] = 0.0;
   const int np = (ncols + 31) / 32;
   if (w < np) load(w);
   for (int t = w; t < np; t += FW) {
@@ -422,11 +447,13 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
 #pragma unroll
     for (int b = 0; b < KT; ++b) s[b] = acc_t{};
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < NJ; j += PH)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int b = 0; b < KT; ++b) s[b] = Tile<CT>::mfma(qr[b][j][i], kb[j][i], s[b]);
+        for (int h = 0; h < PH; ++h)
+#pragma unroll
+          for (int b = 0; b < KT; ++b) s[b] = Tile<CT>::mfma(qr[b][j + h][i], kb[j + h][i], s[b]);
     if (t + FW < np) load(t + FW);
 #pragma unroll
     for (int b = 0; b < KT; ++b)
@@ -439,13 +466,15 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float pr = exp_neg(s[b][e + i] * a.scale - l4[i]);
-          acc += (double)(key <= ps[i] ? pr : 0.f);
+          acc[(e >> 2) % PH] += (double)(key <= ps[i] ? pr : 0.f);
         }
       }
   }
 #pragma unroll
-  for (int i = CT; i < 64; i <<= 1) acc += __shfl_xor(acc, i, 64);
-  if (g == 0) s_sum[w][lc] = acc;
+  for (int h = 0; h < PH; ++h)
+#pragma unroll
+    for (int i = CT; i < 64; i <<= 1) acc[h] += __shfl_xor(acc[h], i, 64);
+  if (g == 0) s_sum[w][lc] = PH == 1 ? acc[0] : acc[0] + acc[PH - 1];
   __syncthreads();
   if (tid < CT && key < rq.T) {
     double t = 0.0;
