@@ -55,18 +55,6 @@ __device__ __forceinline__ void wave_sync() {
 
 __device__ __forceinline__ f32x4_t ld4(const float* p) { return *(const f32x4_t*)p; }
 
-// e^x for x <= 0, -inf included: v_exp_f32 (1 ulp) of y = x log2 e rounded, and what the rounding and
-// the constant's own leave out, r, by 2^r = 1 + r ln 2: within 2 ulp of e^x, in half of expf's
-// instructions.  Without r the error is 2^-24 |x|, which the 512-token layer's scores showed (7.9e-8
-// against 6.5e-8 with expf).  r is kept finite where y is not: 2^y is 0 (or NaN) there.  (Below 2^-126
-// the result is 0.)
-__device__ __forceinline__ float exp_neg(float x) {
-  const float y = x * 1.44269502f;
-  const float r = __builtin_fmaf(x, 1.92596299e-8f, __builtin_fmaf(x, 1.44269502f, -y));
-  const float e = __builtin_amdgcn_exp2f(y);
-  return __builtin_fmaf(e, fminf(fmaxf(r, -1.f), 1.f) * 0.693147181f, e);
-}
-
 // CT x CT tiles of v_mfma_f32: NG lane groups hold one value of the contraction each, a lane owns
 // column lc and rows row_in(e) of the result.
 template <int CT>
@@ -91,9 +79,10 @@ struct Tile {
 // other wave of the SIMD beside the MFMAs.  The column tile is the least work a compute unit can get:
 // 32 columns of 1500 keys at D = 64 take it 20 us, so launches of few tiles use 16 columns, which
 // doubles the K/V reads per column (see the dispatch).
-// Measured: 1500 tokens, 576 rows, 8/2/64 25 us (237 with one wave per row and head on the vector
-// ALU), the 192 probe rows of a 512-token layer 8.6 us (20), 4096 rows of 32/8/128 1.34 ms or
-// 103 TFLOP/s (29 ms).
+// Measured: 1500 tokens, 576 rows, 8/2/64 27 us (237 with one wave per row and head on the vector
+// ALU), the 192 probe rows of a 512-token layer 8.6 us (20), 4096 rows of 32/8/128 1.42 ms or
+// 97 TFLOP/s (29 ms).  expf takes 6 % of that over v_exp_f32 of x log2 e with the product's rounding made up
+// for, which is as exact for probabilities near 1 but drops those below 2^-126.
 template <int D, int CT, bool PAGED, bool PV>
 __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
   constexpr int NG = Tile<CT>::NG, AE = Tile<CT>::AE, PH = Tile<CT>::PH;
@@ -230,7 +219,7 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
     for (int i = CT; i < 64; i <<= 1) mx = fmaxf(mx, __shfl_xor(mx, i, 64));
     const float mn = fmaxf(m, mx);
     if (__ballot(mn > m)) {
-      const float f = mn == -INFINITY ? 1.f : exp_neg(m - mn);
+      const float f = mn == -INFINITY ? 1.f : expf(m - mn);
 #pragma unroll
       for (int h = 0; h < PH; ++h) l[h] *= f;
       if constexpr (PV) {
@@ -244,7 +233,7 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
     const float msub = m == -INFINITY ? 0.f : m;
 #pragma unroll
     for (int x = 0; x < KPP; ++x) {
-      p[x] = exp_neg(p[x] - msub);
+      p[x] = expf(p[x] - msub);
       l[(x >> 2) % PH] += p[x];   // (keys 16 b + 8 h + 4 g ..: part h)
     }
     if constexpr (PV) {
@@ -310,10 +299,10 @@ __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
 #pragma unroll
   for (int i = 0; i < FW; ++i) M = fmaxf(M, ms[i][lc]);
 #pragma unroll
-  for (int i = 0; i < FW; ++i) L += ms[i][lc] == -INFINITY ? ls[i][lc] : ls[i][lc] * exp_neg(ms[i][lc] - M);
+  for (int i = 0; i < FW; ++i) L += ms[i][lc] == -INFINITY ? ls[i][lc] : ls[i][lc] * expf(ms[i][lc] - M);
   const int h = c0 + lc - my_row * a.G;
   if constexpr (PV) {
-    const float f = m == -INFINITY ? 1.f : exp_neg(m - M);   // (no key seen: O is 0, or NaN as L then is)
+    const float f = m == -INFINITY ? 1.f : expf(m - M);   // (no key seen: O is 0, or NaN as L then is)
 #pragma unroll
     for (int j = 0; j < VW; ++j)
 #pragma unroll
@@ -465,7 +454,7 @@ __global__ __launch_bounds__(FW * 64, 1) void colsum_f32_kernel(ColsumF a) {
         const int ps[4] = {p4.x, p4.y, p4.z, p4.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float pr = exp_neg(s[b][e + i] * a.scale - l4[i]);
+          const float pr = expf(s[b][e + i] * a.scale - l4[i]);
           acc[(e >> 2) % PH] += (double)(key <= ps[i] ? pr : 0.f);
         }
       }

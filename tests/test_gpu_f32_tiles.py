@@ -100,3 +100,48 @@ def test_scores_tiles(hq, hkv, d):
                                O.softmax_scale(d))
         have = got[off:off + req.n_tokens]
         assert np.all(np.abs(have - ref) <= 1e-4 * np.abs(ref) + 1e-7), r
+
+
+def test_one_pass_scores_far_from_one():
+    """Probabilities below the normal range count with what float32 holds of them, and those above it are
+    infinite, never NaN.  Tolerance: 1e-4 of the value as above, and half a unit (2^-149) per subnormal probability."""
+    log("[f32 tiles] one-pass scores far from one")
+    specs = [[(33, False, 0, None), (100, True, 7, None), (66, False, 0, None)]]
+    w = W.custom_workload(specs, n_q_heads=8, n_kv_heads=2, head_dim=64, dtype="f32", rope_base=1e4, seed=5)
+    t = W.layer_tensors(w, 0)
+    g = GpuLayer(w, t)
+    g.realign()
+    g.scatter_nonreused()
+    req, scale = w.requests[0], O.softmax_scale(64)
+    keys = O.gather_tokens(req, w, host(g.k_cache)).astype(np.float64)
+    z = np.einsum("ihd,jhd->hij", t["q"].astype(np.float64), np.repeat(keys, 4, 1)) * scale
+    z[:, np.triu(np.ones(z.shape[1:], bool), 1)] = -np.inf
+    lse = np.logaddexp.reduce(z, 2)
+    probes = O.probe_positions(req.n_tokens, req.segments)
+    for shift in (0.0, 90.0, 95.0, -200.0):
+        caller = (lse + shift).T.astype(np.float32)
+        sx.sparseq_score(g.plan, g.t["q"], g.k_cache, g.scores, lse_in=torch.from_numpy(np.ascontiguousarray(caller)).cuda())
+        got = host(g.scores).astype(np.float64)
+        p = np.exp(z[:, probes] - caller.T.astype(np.float64)[:, probes, None])
+        ref = p.sum((0, 1))
+        if shift < 0:
+            assert np.isposinf(got).all()
+        else:
+            assert (np.abs(got - ref) <= 1e-4 * ref + p.shape[0] * p.shape[1] * 2.0 ** -150).all(), shift
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (32, 32)], ids=["narrow", "wide"])
+def test_attention_of_subnormal_probabilities(hq, hkv, d):
+    """A key whose probability is far below the normal range counts when its value is large.  Tolerance: half a
+    unit (2^-150) of a probability of e^-90, 2^-129, is 2^-21 of it; the score's rounding (90 x 2^-23) twice that
+    and more: 1e-4."""
+    log(f"[f32 tiles] subnormal probabilities {hq}/{hkv}/{d}")
+    T = 8 if hq == 1 else 300
+    q, k, v = (np.zeros((T, h, d), np.float32) for h in (hq, hkv, hkv))
+    q[:, :, 0] = np.sqrt(d)
+    k[0, :, 0] = -90.0
+    v[0] = 1e35
+    out, _ = _full(sx.make_desc(hq, hkv, d, "f32", 1e4), q, k, v, (T,))
+    ref = 1e35 * np.exp(-90.0) / np.arange(1, T)
+    assert (np.abs(out[1:] / ref[:, None, None] - 1) <= 1e-4).all()
