@@ -35,14 +35,17 @@ __device__ __forceinline__ int64_t row_index(const ReqDev& rq, const int32_t* ro
 // GEMM on listed rows.  Computed transposed, Y^T = W X^T: the MFMA A operand is a slice of W (16
 // output features), the B operand a slice of X^T (16 rows), so each lane owns one row of the
 // result and writes 4 consecutive features per store.
-// Workgroup tile: BN features x BM rows; WN x WM x WK waves, a wave owns BN / WN features x BM / WM
-// rows of every WK-th 64-wide piece of k.  The MFMA is v_mfma_f32_16x16x32_bf16: measured 1-12 %
-// faster than v_mfma_f32_32x32x16_bf16 on the same tiles, most on the narrow products.  The k
-// dimension moves in stages of WK pieces through NST LDS buffers: both operand tiles go global -> LDS
-// directly (16 bytes per lane); stage t + NST is issued once its readers have read stage t, so a stage
-// has about NST - 1 stages of compute to land.  A tile row (64 bf16) holds 8 chunks of 16 bytes,
-// XOR-swizzled per row (chunk_swz) so that the rows a read instruction touches at one logical chunk hit
-// distinct banks.  The WK partial sums are added through LDS in order.
+// Workgroup tile: BN features x BM rows; WN x WM waves, a wave owns BN / WN features x BM / WM rows.  The
+// MFMA is v_mfma_f32_16x16x32_bf16: measured 1-12 % faster than v_mfma_f32_32x32x16_bf16 on the same
+// tiles, most on the narrow products.  The k dimension moves in stages of 64 through NST LDS buffers:
+// both operand tiles go global -> LDS directly (16 bytes per lane); stage t + NST is issued once its
+// readers have read stage t, so a stage has about NST - 1 stages of compute to land.  A tile row (64 bf16)
+// holds 8 chunks of 16 bytes, XOR-swizzled per row (chunk_swz) so that the rows a read instruction touches
+// at one logical chunk hit distinct banks.
+// Every tile sums an element over k in one order, MFMA after MFMA, so a row's result does not depend on
+// the tile that the launch's size chose.  Two or four wave groups that share k on the small tiles, their
+// sums added at the end, were no faster (394 rows, 4096 -> 4096 features: 26.3 / 27.2 us in two groups;
+// 200 rows 20.2 / 20.7 in four).
 // Matrix-core bound on 256 x 256 tiles with many rows (gate_up of 6712 rows, 4096 -> 28672: 1252 us,
 // 1.26 PFLOP/s, 1370 with a stage's transfers issued together); with few rows a tile per compute unit
 // bounds it (see the dispatch).
@@ -69,24 +72,22 @@ struct GemmRowsK {
 // read at one logical chunk cover the 16 four-bank groups of a 256-byte LDS line
 __device__ __forceinline__ int chunk_swz(int c, int row) { return c ^ ((row >> 1) & 7); }   // (two rows per line)
 
-template <int BN, int BM, int WN, int WM, int WK, int NST>
-__global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRowsK a) {
-  constexpr int NG = WN * WM;                  // waves that share a piece of k
+template <int BN, int BM, int WN, int WM, int NST>
+__global__ __launch_bounds__(WN * WM * 64, 1) void gemm_rows_kernel(GemmRowsK a) {
+  constexpr int NW = WN * WM;
   constexpr int FI = BN / WN / 16;             // 16-feature fragments per wave
   constexpr int RJ = BM / WM / 16;             // 16-row fragments per wave
   constexpr int ROWB = 128;                    // bytes of one tile row (64 bf16)
   constexpr int CH = ROWB / 16;                // 16-byte chunks per row
   constexpr int RPT = 1024 / ROWB;             // rows per 1 KB transfer
-  constexpr int PIECE = (BN + BM) * ROWB;      // one piece of both operands
-  constexpr int STAGE = WK * PIECE;
-  constexpr int PW = BN / RPT / NG, PX = BM / RPT / NG;   // transfers per wave and operand
-  static_assert(PW * NG * RPT == BN && PX * NG * RPT == BM, "transfers spread evenly over the waves");
+  constexpr int STAGE = (BN + BM) * ROWB;
+  constexpr int PW = BN / RPT / NW, PX = BM / RPT / NW;   // transfers per wave and operand
+  static_assert(PW * NW * RPT == BN && PX * NW * RPT == BM, "transfers spread evenly over the waves");
   static_assert(kGemmPart % BN == 0, "a tile lies in one output part");
-  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];   // [stage][piece][W | X]
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];   // [stage][W | X]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wall = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wk = wall / NG, wu = wall % NG;
+  const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
   // tile order: groups of kGemmGM row tiles, the feature tile slowest within a group, so that a run of
   // consecutive tile indices covers a few feature tiles x all row tiles of the group.  The hardware
   // deals block b to XCD b mod 8; each XCD takes a contiguous run of tile indices, so the workgroups
@@ -111,29 +112,26 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
 
   // ---- transfers: 1 KB holds rows RPT q .. RPT q + RPT - 1 of a tile; lane l fills row RPT q + l / CH,
   // physical chunk l % CH with the logical chunk that chunk_swz maps there.  A wave moves transfers
-  // wu + NG i of both tiles of its group's piece. ----
+  // wu + NW i of both tiles. ----
   const uint16_t* src[PW + PX];
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
-    const int row = RPT * (wu + NG * i) + lane / CH;
-    src[i] = a.w + (int64_t)(n0 + row) * K + wk * 64 + chunk_swz(lane % CH, row) * 8;   // (an involution)
+    const int row = RPT * (wu + NW * i) + lane / CH;
+    src[i] = a.w + (int64_t)(n0 + row) * K + chunk_swz(lane % CH, row) * 8;   // (an involution)
   }
 #pragma unroll
   for (int i = 0; i < PX; ++i) {
-    const int row = RPT * (wu + NG * i) + lane / CH;
+    const int row = RPT * (wu + NW * i) + lane / CH;
     const int m = min(m0 + row, nr - 1);   // rows past the request's last read a valid row
-    src[PW + i] = a.x + row_index(rq, a.rows, m, a.x_tok) * K + wk * 64 + chunk_swz(lane % CH, row) * 8;
+    src[PW + i] = a.x + row_index(rq, a.rows, m, a.x_tok) * K + chunk_swz(lane % CH, row) * 8;
   }
-  const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)(wk * PIECE);
-  // stages of the workgroup, and those that hold a piece for this wave's group (a group may have one
-  // fewer when the pieces do not divide by WK)
-  const int nT = (K / 64 + WK - 1) / WK;
-  const int nk = (K / 64 - wk + WK - 1) / WK;
+  const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const int nk = K / 64;
   // transfer d of this wave for stage t, into buffer t mod NST
   auto dma = [&](int t, int d) {
     const uint32_t m0r = __builtin_amdgcn_readfirstlane(smem_lds + (uint32_t)((t % NST) * STAGE) +
-                                                        (uint32_t)(d < PW ? (wu + NG * d) * 1024 : BN * ROWB + (wu + NG * (d - PW)) * 1024));
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src[d] + t * WK * 64), "s"(m0r) : "m0", "memory");
+                                                        (uint32_t)(d < PW ? (wu + NW * d) * 1024 : BN * ROWB + (wu + NW * (d - PW)) * 1024));
+    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src[d] + t * 64), "s"(m0r) : "m0", "memory");
   };
   // wait until this wave's transfers of every stage before the n youngest have landed
   auto wait_stages = [&](int n) {
@@ -148,11 +146,11 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
   };
   // Before stage t is read: this wave's transfers of it have landed (the younger ones may be in flight),
   // its reads of the stages before are done (the barrier alone does not wait for them), and so are the
-  // other waves' of the group (one wave needs no barrier); past it the buffer of stage t - 1 is free.
+  // other waves'; past it the buffer of stage t - 1 is free.
   auto enter_stage = [&](int t) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     wait_stages(min(NST - 2, nk - 1 - t));
-    if constexpr (NG > 1) __syncthreads();
+    __syncthreads();
   };
 
   // ---- operand reads: a lane reads row lr of each 16-row fragment, 16 bytes of k starting at chunk
@@ -231,8 +229,8 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
 #pragma unroll
       for (int d = 0; d < ND; ++d) dma(t, d);
   wait_stages(min(NST - 1, nk - 1));   // stage 0 has landed
-  if constexpr (NG > 1) __syncthreads();
-  if (nk > 0) {
+  __syncthreads();
+  {
     const uint32_t wb = smem_lds + lane_off[0] + (uint32_t)(wn * FI * 16 * ROWB);
     const uint32_t xb = smem_lds + (uint32_t)(BN * ROWB) + lane_off[0] + (uint32_t)(wm * RJ * 16 * ROWB);
 #pragma unroll
@@ -252,21 +250,6 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
     phase(c0, yes, no, t, c1, no, 0);
     phase(c1, no, no, 0, c0, no, 0);
   }
-  if (NG > 1 && WK > 1 && nk < nT && nT > 1) __syncthreads();   // (a group with one stage fewer passes as many)
-
-  // ---- sum over the k groups: every wave leaves its accumulators in LDS and adds up those of its
-  // share of the fragments (FS of them), group by group ----
-  constexpr int FS = FI * RJ / WK;   // fragments a wave finishes
-  static_assert(FS * WK == FI * RJ && (WK == 1 || WK * BN * BM * 4 <= NST * STAGE), "fragments spread evenly and fit the stage buffers");
-  f32x4_t* const part = (f32x4_t*)smem;
-  if constexpr (WK > 1) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < FI; ++i)
-#pragma unroll
-      for (int j = 0; j < RJ; ++j) part[((wk * NG + wu) * FI * RJ + i * RJ + j) * 64 + lane] = acc[i][j];
-    __syncthreads();
-  }
 
   // ---- epilogue: lane owns row 16 j + lr of the wave's rows; value e of accumulator (i, j) is feature
   // 16 i + 4 cg + e of the wave's features.  Part boundaries are multiples of the tile width, so the
@@ -276,22 +259,13 @@ __global__ __launch_bounds__(WN * WM * WK * 64, 1) void gemm_rows_kernel(GemmRow
   uint16_t* const yp = a.y[op];
   const int ld = a.pn[op + 1] - a.pn[op];
   const int col0 = n0 - a.pn[op] + wn * FI * 16 + 4 * cg;
-  const int f0 = WK > 1 ? wk * FS : 0;
 #pragma unroll
-  for (int f = 0; f < FS; ++f) {
-    // (row major over the fragments that the wave keeps, feature major over a share of them)
-    const int i = WK > 1 ? (f0 + f) / RJ : f % FI, j = WK > 1 ? (f0 + f) % RJ : f / FI;
+  for (int f = 0; f < FI * RJ; ++f) {
+    const int i = f % FI, j = f / FI;
     const int m = m0 + wm * RJ * 16 + 16 * j + lr;
     if (m >= nr) continue;
     const int64_t yr = row_index(rq, a.rows, m, a.y_tok) * ld + col0 + 16 * i;
-    f32x4_t v;
-    if constexpr (WK > 1) {
-      v = part[(wu * FI * RJ + f0 + f) * 64 + lane];
-#pragma unroll
-      for (int g = 1; g < WK; ++g) v += part[((g * NG + wu) * FI * RJ + f0 + f) * 64 + lane];
-    } else {
-      v = acc[f % FI][f / FI];
-    }
+    f32x4_t v = acc[i][j];
     if (a.res) {
       const uint2 rv = *(const uint2*)(a.res + yr);
       v[0] += bf16_lo(rv.x);
@@ -473,12 +447,12 @@ __global__ __launch_bounds__(256) void silu_mul_rows_kernel(const ReqDev* __rest
 
 }  // namespace
 
-template <int BN, int BM, int WN, int WM, int WK, int NST>
+template <int BN, int BM, int WN, int WM, int NST>
 static hipError_t launch_gemm_tiles(GemmRowsK& a, hipStream_t s) {
   a.m_tiles = (a.max_rows + BM - 1) / BM;
   const int64_t tiles = (int64_t)a.m_tiles * a.n_req * (a.N / BN);
   const int64_t blocks = (tiles + kGemmXcds - 1) / kGemmXcds * kGemmXcds;
-  hipLaunchKernelGGL((gemm_rows_kernel<BN, BM, WN, WM, WK, NST>), dim3((unsigned)blocks), dim3(WN * WM * WK * 64), 0, s, a);
+  hipLaunchKernelGGL((gemm_rows_kernel<BN, BM, WN, WM, NST>), dim3((unsigned)blocks), dim3(WN * WM * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -529,11 +503,11 @@ hipError_t launch_gemm_rows(const sx_plan* p, const RowsArg& r, const void* x, i
     }
   }
   switch (best) {
-    case 0: return launch_gemm_tiles<256, 256, 4, 2, 1, 2>(a, s);
-    case 1: return launch_gemm_tiles<256, 128, 4, 2, 1, 3>(a, s);
-    case 2: return launch_gemm_tiles<128, 128, 4, 2, 1, 4>(a, s);
-    case 3: return launch_gemm_tiles<128, 64, 2, 2, 2, 3>(a, s);
-    default: return launch_gemm_tiles<64, 64, 1, 1, 4, 2>(a, s);
+    case 0: return launch_gemm_tiles<256, 256, 4, 2, 2>(a, s);
+    case 1: return launch_gemm_tiles<256, 128, 4, 2, 3>(a, s);
+    case 2: return launch_gemm_tiles<128, 128, 4, 2, 4>(a, s);
+    case 3: return launch_gemm_tiles<128, 64, 4, 2, 4>(a, s);
+    default: return launch_gemm_tiles<64, 64, 2, 2, 4>(a, s);
   }
 }
 

@@ -73,3 +73,45 @@ def test_float32_tile_width(hq, hkv, d, lengths):
     log(f"[batch bits] f32 {hq}/{hkv}/{d} {lengths}")
     g = hq // hkv
     _attention_bits(_work(hq, hkv, d, lengths, "f32"), lambda rows, keys, n: (rows * g + 31) // 32 * hkv * n >= 256)
+
+
+def _tile(rows, n, requests):
+    """The product tile (features x rows) of the library's rule."""
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    best = None
+    for bn, bm, cost in ((256, 256, 1.5), (256, 128, 0.95), (128, 128, 0.60), (128, 64, 0.46), (64, 64, 0.35)):
+        c = -(-(-(-rows // bm) * requests * (n // bn)) // cu) * cost
+        if best is None or c < 0.98 * best[0]:
+            best = (c, (bn, bm))
+    return best[1]
+
+
+# rows of the request (of eight times as many tokens) and of the batch's others, features, k: every tile among
+# the calls of all cases, more than one in each
+@pytest.mark.parametrize("rows,others,n,k", [(60, (900, 800, 700), 4096, 192), (200, (120,) * 9, 6144, 320),
+                                             (255, (40,) * 3, 512, 704), (129, (100, 300), 28672, 128)],
+                         ids=lambda x: str(x).replace(" ", "")[:16])
+def test_products(rows, others, n, k):
+    log(f"[batch bits] product of {rows} rows with {others}, {k} -> {n}")
+    tokens, counts = (8 * rows,) + others, (rows,) + others
+    w = W.custom_workload([[(t, False, 0, None)] for t in tokens], n_q_heads=8, n_kv_heads=2, head_dim=128, dtype="bf16", rope_base=1e4)
+    gen = torch.Generator().manual_seed(n + rows)
+    x = torch.randn((w.total_tokens, k), generator=gen).bfloat16().cuda()
+    wt = (torch.randn((n, k), generator=gen) / k ** 0.5).bfloat16().cuda()
+    res = torch.randn((w.total_tokens, n), generator=gen).bfloat16().cuda()
+    row = torch.cat([torch.arange(t, dtype=torch.int32) for t in tokens]).cuda()
+    cnt = torch.tensor(counts, dtype=torch.int32, device="cuda")
+    got, tiles = [], set()
+    for many, bound in ((1, rows), (1, 8 * rows), (len(counts), max(counts)), (len(counts), max(tokens))):
+        plan = sx.Plan(desc_of(w), w.requests[:many], w.n_dst_blocks, w.n_src_blocks)
+        y = torch.zeros((w.total_tokens, n), dtype=torch.bfloat16, device="cuda")
+        sx.gemm_rows(plan, row, cnt, bound, x, wt, y, residual=res)
+        torch.cuda.synchronize()
+        got.append(y[:rows])
+        tiles.add(_tile(bound, n, many))
+        plan.close()
+    assert len(tiles) > 1, tiles
+    for y in got[1:]:
+        assert torch.equal(y, got[0])
+    ref = x[:rows].float() @ wt.float().t() + res[:rows].float()
+    assert (got[0].float() - ref).abs().max() <= 2.0 ** -7 * ref.abs().max()
