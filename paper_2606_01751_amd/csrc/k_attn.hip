@@ -74,37 +74,8 @@ struct AttnK {
   const int32_t* order;
 };
 
-typedef short shortx4_t __attribute__((ext_vector_type(4)));
-
-// XOR applied to the 16-byte chunk index of row r of a V tile.  Each transposed read touches 4
-// consecutive rows; this spreads their 32-byte (per 16 lanes) and 64-byte (per 32 lanes) pieces over
-// distinct banks for both 128- and 256-byte-per-clock LDS service.  D = 64 rows have 8 chunks.
-template <int NCH>
-__device__ __forceinline__ int v_swz(int r) {
-  return NCH >= 16 ? ((0xCA60 >> ((r & 3) * 4)) & 15) : ((0x4260 >> ((r & 3) * 4)) & 7);
-}
-typedef __attribute__((address_space(3))) shortx4_t lds_shortx4_t;
-
 // s_waitcnt with vmcnt <= n (n < 16), expcnt and lgkmcnt left unconstrained (gfx9 encoding).
 #define SX_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (0x7 << 4) | (0xF << 8))
-// Scheduling groups (instruction classes of the sched_group_barrier builtin): the next `n`
-// instructions of class `mask` are placed here, in program order of the groups.
-#define SX_SG(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
-constexpr int kSgValu = 0x2, kSgMfma = 0x8, kSgDsRead = 0x100;
-// Order of a matrix phase of NM MFMAs whose operands come from NR LDS reads each: the reads of
-// the first PRE MFMAs go first, then every MFMA is followed by the reads of the MFMA PRE places
-// later, so each read has PRE MFMAs (32 cycles each) to complete.
-template <int NM, int NR, int PRE>
-__device__ __forceinline__ void sched_pipelined() {
-  SX_SG(kSgDsRead, NR * PRE);
-#pragma unroll
-  for (int i = 0; i < NM - PRE; ++i) {
-    SX_SG(kSgMfma, 1);
-    SX_SG(kSgDsRead, NR);
-  }
-  SX_SG(kSgMfma, PRE);
-}
-
 // The kernel arguments for one item of a persistent kernel: read from the kernel-argument segment
 // (where the by-value argument sits at offset 0) through a pointer the compiler cannot follow, so
 // the loads stay inside the item and nothing of them is kept across items.

@@ -54,7 +54,6 @@ constexpr int kGemmMaxParts = 4;
 constexpr int kGemmGM = 8;          // row tiles per group of the tile order
 constexpr int kGemmPart = 256;      // widths are multiples of this (a tile lies in one output part)
 constexpr unsigned kGemmXcds = 8;   // XCDs of the chip, which deals workgroups round-robin
-constexpr int kSgMfma = 0x8, kSgDsRead = 0x100;   // sched_group_barrier instruction classes
 
 struct GemmRowsK {
   const ReqDev* reqs;

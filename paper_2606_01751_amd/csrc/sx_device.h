@@ -91,6 +91,35 @@ __device__ __forceinline__ int lower_bound_wave(const int32_t* x, int n, int v, 
   return lo;
 }
 
+typedef short shortx4_t __attribute__((ext_vector_type(4)));
+
+// XOR applied to the 16-byte chunk index of row r of a V tile.  Each transposed read touches 4
+// consecutive rows; this spreads their 32-byte (per 16 lanes) and 64-byte (per 32 lanes) pieces over
+// distinct banks for both 128- and 256-byte-per-clock LDS service.  D = 64 rows have 8 chunks.
+template <int NCH>
+__device__ __forceinline__ int v_swz(int r) {
+  return NCH >= 16 ? ((0xCA60 >> ((r & 3) * 4)) & 15) : ((0x4260 >> ((r & 3) * 4)) & 7);
+}
+typedef __attribute__((address_space(3))) shortx4_t lds_shortx4_t;
+
+// Scheduling groups (instruction classes of the sched_group_barrier builtin): the next `n`
+// instructions of class `mask` are placed here, in program order of the groups.
+#define SX_SG(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
+constexpr int kSgMfma = 0x8, kSgDsRead = 0x100;
+// Order of a matrix phase of NM MFMAs whose operands come from NR LDS reads each: the reads of
+// the first PRE MFMAs go first, then every MFMA is followed by the reads of the MFMA PRE places
+// later, so each read has PRE MFMAs (32 cycles each) to complete.
+template <int NM, int NR, int PRE>
+__device__ __forceinline__ void sched_pipelined() {
+  SX_SG(kSgDsRead, NR * PRE);
+#pragma unroll
+  for (int i = 0; i < NM - PRE; ++i) {
+    SX_SG(kSgMfma, 1);
+    SX_SG(kSgDsRead, NR);
+  }
+  SX_SG(kSgMfma, PRE);
+}
+
 // Pool offset (elements) of (slot, head) in a [blocks][Hkv][16][D] pool.
 __device__ __forceinline__ int64_t pool_off(int32_t slot, int head, int Hkv, int D) {
   return ((((int64_t)(slot >> 4)) * Hkv + head) * 16 + (slot & 15)) * (int64_t)D;

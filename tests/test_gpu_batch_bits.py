@@ -75,6 +75,72 @@ def test_float32_tile_width(hq, hkv, d, lengths):
     _attention_bits(_work(hq, hkv, d, lengths, "f32"), lambda rows, keys, n: (rows * g + 31) // 32 * hkv * n >= 256)
 
 
+def attention_route(rows, keys, requests, hq, hkv, d):
+    """The kernel of a bfloat16 attention of so many rows per request: the 256-column grid (0), or workgroups of
+    so many waves for 32 columns."""
+    rpw = 256 // (hq // hkv)
+    tiles = -(-rows // rpw) * hkv * requests
+    if tiles * d // 128 > (140 if d == 128 else 90) + 80000 // max(1, keys):
+        return 0
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    return 2 if d == 64 and tiles * -(-rpw * (hq // hkv) // 32) > 4 * cu else 4
+
+
+# the request alone in 32-column workgroups (of four waves), the batch in the 256-column grid, and at the end in
+# those of two waves: group sizes that do and do not divide 256 and 32, both head dims, partial last rounds (128
+# keys, 64 with two waves) and key tiles
+@pytest.mark.parametrize("hq,hkv,d,lengths", [
+    (32, 8, 128, (600,) + (500, 550, 3, 640) * 2), (28, 4, 128, (701,) + (650,) * 6), (8, 2, 128, (385,) + (800,) * 20),
+    (64, 16, 64, (700,) + (650, 690) * 3), (33, 1, 64, (129,) + (650,) * 12), (8, 8, 64, (63,) + (1000,) * 25),
+    (64, 1, 128, (31,) + (300,) * 9), (16, 4, 64, (97,) + (120,) * 40), (6, 2, 64, (200,) + (64, 130) * 60)], ids=lambda x: str(x).replace(" ", "")[:24])
+def test_bfloat16_attention(hq, hkv, d, lengths):
+    log(f"[batch bits] bf16 {hq}/{hkv}/{d} {lengths}")
+    _attention_bits(_work(hq, hkv, d, lengths, "bf16"), lambda rows, keys, n: attention_route(rows, keys, n, hq, hkv, d))
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (28, 4, 128), (16, 4, 64)])
+def test_bfloat16_attention_of_growing_scores(hq, hkv, d):
+    """Scores that outgrow the running maximum again and again (by more than 2^64 in the probability): in the first
+    and the second half of either key tile of a round, in both tiles of one, from a first tile of -inf on; and
+    infinite scores and values.  One request in 32-column workgroups and many in the 256-column grid."""
+    log(f"[batch bits] growing scores {hq}/{hkv}/{d}")
+    T, n = 640, 24
+    gen = torch.Generator().manual_seed(d)
+    base = [torch.randn((T, h, d), generator=gen) for h in (hq, hkv, hkv)]
+    desc = sx.make_desc(hq, hkv, d, "bf16", 1e4)
+    assert attention_route(T, T, 1, hq, hkv, d) and not attention_route(T, T, n, hq, hkv, d)
+    # steps: (key, score in units of log2 e from there on), by a dimension that only this uses
+    for steps, odd in (([(70, 90.0)], None), ([(100, 90.0), (161, 200.0)], None), ([(200, 100.0), (260, 190.0), (330, 400.0)], None),
+                       ([(0, -900.0), (64, -500.0), (128, -300.0), (192, -100.0), (300, 0.0)], None), ([(600, 80.0)], None),
+                       ([(0, -float("inf")), (64, 0.0)], None), ([(0, -float("inf")), (150, 0.0), (400, 100.0)], None),
+                       ([(0, 0.0)], ("k", 500, float("inf"))), ([(0, 0.0)], ("v", 77, float("nan"))), ([(0, 0.0)], ("v", 639, float("inf")))):
+        q, k, v = (x.clone() for x in base)
+        q[..., 0] = 1.0
+        k[..., 0] = 0.0
+        for key, z in steps:
+            k[key:, :, 0] = z * d ** 0.5
+        if odd:
+            (k if odd[0] == "k" else v)[odd[1], 0, 1] = odd[2]
+        one = [x.bfloat16().cuda() for x in (q, k, v)]
+        many = [x.repeat(n, 1, 1) for x in one]
+        got = []
+        for cnt, t in ((1, one), (n, many)):
+            cu = torch.arange(0, T * cnt + 1, T, dtype=torch.int32, device="cuda")
+            out, lse = torch.zeros_like(t[0]), torch.zeros(t[0].shape[:2], dtype=torch.float32, device="cuda")
+            sx.full_attn(desc, *t, cu, cnt, T, out, lse)
+            torch.cuda.synchronize()
+            got.append((out, lse))
+        (a, la), (b, lb) = got
+        for r in (0, n - 1):
+            for x, y in ((a, b[r * T:(r + 1) * T]), (la, lb[r * T:(r + 1) * T])):
+                assert torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(7.0), y.nan_to_num(7.0)), (steps, odd)
+        if odd is None and steps[0][1] > -1e30:
+            z = torch.einsum("ihd,jhd->hij", one[0].double().cpu(), one[1].double().cpu().repeat_interleave(hq // hkv, 1)) * d ** -0.5
+            z.masked_fill_(torch.ones(T, T, dtype=torch.bool).triu(1), -float("inf"))
+            ref = torch.einsum("hij,jhd->ihd", z.softmax(-1), one[2].double().cpu().repeat_interleave(hq // hkv, 1))
+            assert (a.double().cpu() - ref).abs().max() <= 4e-2, steps
+
+
 def _tile(rows, n, requests):
     """The product tile (features x rows) of the library's rule."""
     cu = torch.cuda.get_device_properties(0).multi_processor_count
