@@ -11,6 +11,7 @@
 // move K and V through LDS (global -> LDS, whole rows; K read straight into operand registers, 32 bytes of
 // each of 32 rows per instruction, cost the address unit three times as long).
 #include <algorithm>
+#include <type_traits>
 
 #include "sx_device.h"
 #include "sx_internal.h"
@@ -22,7 +23,7 @@ namespace {
 // fastest the round-robin dispatch over the 8 XCDs keeps a head's K and V in one L2 (8 heads) or a few.
 constexpr int kTilesX = 64;
 constexpr int COLS = 256;   // columns of a row tile of k_attn.hip
-constexpr int SW = 4;       // waves per workgroup
+constexpr int SW = 4;       // waves per workgroup of the log-sum-exp pass
 
 struct AttnS {
   const uint16_t* q;
@@ -47,13 +48,14 @@ struct AttnS {
 // waves: wave w forms S and the probabilities of 32 of the round's 32 NW keys, passes P^T on through LDS, and
 // adds P.V of the whole round to 32 dims of O^T (waves past D / 32 rest then).  Only the sum of a tile's
 // probabilities is serial: its second half goes on from the first half's.
-// Bound by a column's chain of rounds while few workgroups run (1.5 us per 128 keys: S 0.2, transfers into
-// LDS 0.2 and 0.25 (22 cycles per 1 KB and compute unit), probabilities 0.35, P.V 0.25, the rest barriers and the
-// LDS trips behind them), by those transfers, K and V whole for every 32 columns, once the chip is full.
-// Two buffers for K and V (one workgroup per compute unit at d = 128) and transfers placed between the
-// MFMAs and exponentials were no faster.  Measured (whole calls, this / the 256-column grid / four waves that
+// Bound by a column's chain of rounds while few workgroups run (1.5 us per 128 keys with 4 waves: S 0.2,
+// transfers into LDS 0.2 and 0.25 (22 cycles per 1 KB and compute unit), probabilities 0.35, P.V 0.25, the rest
+// barriers and the LDS trips behind them), by those transfers, K and V whole for every 32 columns, once the
+// chip is full: hence three widths (see the dispatch).  Two buffers for K and V and transfers placed between
+// the MFMAs and exponentials were no faster.  Measured (whole calls, this / the 256-column grid / four waves that
 // split the keys and merge, whose sums were others): 777 tokens, 388 rows of 32/8/128 15.9 / 28.3 / 14.8 us,
-// 777 rows 19.5 / 29.6 / 21.2, 600 rows of 6000 tokens 79 / 120 / 69, six requests of 250 21 / 29 / 22.
+// 777 rows 19.5 / 29.6 / 21.2, 1200 rows of 6000 tokens of 8/2/128 57 / 124 / 62, six requests of 250 tokens
+// 21 / 29 / 22.
 template <int D, bool PAGED, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(AttnS a) {
   constexpr int KR = 32 * NW;               // keys per round
@@ -496,23 +498,32 @@ hipError_t launch_d(const AttnLaunch& L, bool paged, hipStream_t s) {
   a.grid_rows = L.grid_rows;
   a.scale_log2 = L.scale * 1.4426950408889634f;
   a.lse_base2 = L.lse_base2;
-  const int rpw = COLS / a.G;
-  const int64_t tiles = L.out ? (int64_t)((L.grid_rows + rpw - 1) / rpw) * ((rpw * a.G + 31) / 32) : ((int64_t)L.grid_rows * a.G + 31) / 32;
+  // groups of 32 columns of one request and KV head
+  const int rpw = COLS / a.G, gpt = (rpw * a.G + 31) / 32;
+  const int64_t tiles = L.out ? (int64_t)(L.grid_rows / rpw) * gpt + ((int64_t)(L.grid_rows % rpw) * a.G + 31) / 32
+                              : ((int64_t)L.grid_rows * a.G + 31) / 32;
   const dim3 grid((unsigned)(L.Hkv * std::min<int64_t>(tiles, kTilesX)), (unsigned)((tiles + kTilesX - 1) / kTilesX),
                   (unsigned)L.n_req);
-  if (L.out && D == 64) {
-    // d = 64 keeps 2 of 4 waves busy in P.V: 4 waves halve the rounds of a column, 2 carry more columns at a
-    // time, which counts from about four workgroups per compute unit (16/4/64, 2 / 4 waves: 768 groups of 32
-    // columns of 1500 tokens 27.9 / 24.0 us, 832 of 777 17.2 / 14.8, 960 of 800 17.9 / 18.4, 1536 of 300 11.9 / 15.7)
-    const int64_t groups = tiles * L.Hkv * L.n_req;
-    const bool two = groups > 4 * std::max(1, L.n_cu);
-    if (two && paged) hipLaunchKernelGGL((attn_short_kernel<64, true, 2>), grid, dim3(128), 0, s, a);
-    else if (two) hipLaunchKernelGGL((attn_short_kernel<64, false, 2>), grid, dim3(128), 0, s, a);
-    if (two) return hipGetLastError();
+  if (!L.out) {
+    hipLaunchKernelGGL(lse_short_kernel<D>, grid, dim3(SW * 64), 0, s, a);
+    return hipGetLastError();
   }
-  if (!paged) hipLaunchKernelGGL((attn_short_kernel<D, false, 4>), grid, dim3(256), 0, s, a);
-  else if (L.out) hipLaunchKernelGGL((attn_short_kernel<D, true, 4>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(lse_short_kernel<D>, grid, dim3(SW * 64), 0, s, a);
+  // Waves: the more, the fewer rounds a column takes, and the fewer columns a compute unit carries (LDS: one
+  // workgroup of 8, two of 4 at d = 128 and three at 64, seven of 2), so 8 up to 1.5 groups per compute unit and
+  // 4 beyond; d = 64, where only 2 waves have P.V, 2 from four groups per compute unit.  Measured, 8 / 4 waves:
+  // 8/2/128, 300 groups of 6000 tokens 57 / 73 us, 376 of 1500 19.4 / 23.8, 392 of 777 16.4 / 17.7; 480 of 800
+  // 21.8 / 16.5, 600 of 3000 (32/8) 47.5 / 43.0; 8/8/64, 384 of 3000 25.4 / 32.8, 600 (16/4) 38 / 34; 16/4/64, 4 / 2
+  // waves: 684 of 1500 24.0 / 27.9, 784 of 777 14.8 / 17.2, 960 of 800 18.4 / 17.9, 1216 of 300 15.7 / 11.9.
+  const int64_t groups = tiles * L.Hkv * L.n_req, n_cu = std::max(1, L.n_cu);
+  const int nw = 2 * groups <= 3 * n_cu ? 8 : D == 64 && groups > 4 * n_cu ? 2 : 4;
+  auto go = [&](auto waves) {
+    constexpr int NW = decltype(waves)::value;
+    if (paged) hipLaunchKernelGGL((attn_short_kernel<D, true, NW>), grid, dim3(NW * 64), 0, s, a);
+    else hipLaunchKernelGGL((attn_short_kernel<D, false, NW>), grid, dim3(NW * 64), 0, s, a);
+  };
+  if (nw == 8) go(std::integral_constant<int, 8>{});
+  else if (nw == 4) go(std::integral_constant<int, 4>{});
+  else if constexpr (D == 64) go(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

@@ -82,33 +82,38 @@ def attention_route(rows, keys, requests, hq, hkv, d):
     tiles = -(-rows // rpw) * hkv * requests
     if tiles * d // 128 > (140 if d == 128 else 90) + 80000 // max(1, keys):
         return 0
-    cu = torch.cuda.get_device_properties(0).multi_processor_count
-    return 2 if d == 64 and tiles * -(-rpw * (hq // hkv) // 32) > 4 * cu else 4
+    cu, g = torch.cuda.get_device_properties(0).multi_processor_count, hq // hkv
+    groups = (rows // rpw * -(-rpw * g // 32) + -(-(rows % rpw) * g // 32)) * hkv * requests
+    return 8 if 2 * groups <= 3 * cu else 2 if d == 64 and groups > 4 * cu else 4
 
 
-# the request alone in 32-column workgroups (of four waves), the batch in the 256-column grid, and at the end in
-# those of two waves: group sizes that do and do not divide 256 and 32, both head dims, partial last rounds (128
-# keys, 64 with two waves) and key tiles
+# the request alone in 32-column workgroups of eight or four waves, the batch in the 256-column grid, and at the end
+# in those of four and two waves: group sizes that do and do not divide 256 and 32, both head dims, partial last
+# rounds (256, 128 and 64 keys) and key tiles
 @pytest.mark.parametrize("hq,hkv,d,lengths", [
     (32, 8, 128, (600,) + (500, 550, 3, 640) * 2), (28, 4, 128, (701,) + (650,) * 6), (8, 2, 128, (385,) + (800,) * 20),
     (64, 16, 64, (700,) + (650, 690) * 3), (33, 1, 64, (129,) + (650,) * 12), (8, 8, 64, (63,) + (1000,) * 25),
-    (64, 1, 128, (31,) + (300,) * 9), (16, 4, 64, (97,) + (120,) * 40), (6, 2, 64, (200,) + (64, 130) * 60)], ids=lambda x: str(x).replace(" ", "")[:24])
+    (64, 1, 128, (31,) + (300,) * 9), (16, 4, 64, (97,) + (120,) * 40), (6, 2, 64, (200,) + (64, 130) * 60),
+    (8, 2, 128, (300,) + (290, 257) * 4)], ids=lambda x: str(x).replace(" ", "")[:24])
 def test_bfloat16_attention(hq, hkv, d, lengths):
     log(f"[batch bits] bf16 {hq}/{hkv}/{d} {lengths}")
     _attention_bits(_work(hq, hkv, d, lengths, "bf16"), lambda rows, keys, n: attention_route(rows, keys, n, hq, hkv, d))
 
 
-@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (28, 4, 128), (16, 4, 64)])
-def test_bfloat16_attention_of_growing_scores(hq, hkv, d):
+# requests per launch: workgroups of eight, four and (d = 64) two waves, and the 256-column grid
+@pytest.mark.parametrize("hq,hkv,d,counts", [(8, 2, 128, {1: 8, 3: 4, 24: 0}), (14, 2, 128, {1: 8, 2: 4, 24: 0}),
+                                             (16, 4, 64, {1: 8, 2: 4, 4: 2, 24: 0})], ids=["g4", "g7", "d64"])
+def test_bfloat16_attention_of_growing_scores(hq, hkv, d, counts):
     """Scores that outgrow the running maximum again and again (by more than 2^64 in the probability): in the first
-    and the second half of either key tile of a round, in both tiles of one, from a first tile of -inf on; and
-    infinite scores and values.  One request in 32-column workgroups and many in the 256-column grid."""
+    and the second half of any key tile of a round, in several of one, from a first tile of -inf on; and
+    infinite scores and values."""
     log(f"[batch bits] growing scores {hq}/{hkv}/{d}")
-    T, n = 640, 24
+    T = 640
     gen = torch.Generator().manual_seed(d)
     base = [torch.randn((T, h, d), generator=gen) for h in (hq, hkv, hkv)]
     desc = sx.make_desc(hq, hkv, d, "bf16", 1e4)
-    assert attention_route(T, T, 1, hq, hkv, d) and not attention_route(T, T, n, hq, hkv, d)
+    for n, waves in counts.items():
+        assert attention_route(T, T, n, hq, hkv, d) == waves
     # steps: (key, score in units of log2 e from there on), by a dimension that only this uses
     for steps, odd in (([(70, 90.0)], None), ([(100, 90.0), (161, 200.0)], None), ([(200, 100.0), (260, 190.0), (330, 400.0)], None),
                        ([(0, -900.0), (64, -500.0), (128, -300.0), (192, -100.0), (300, 0.0)], None), ([(600, 80.0)], None),
@@ -122,18 +127,19 @@ def test_bfloat16_attention_of_growing_scores(hq, hkv, d):
         if odd:
             (k if odd[0] == "k" else v)[odd[1], 0, 1] = odd[2]
         one = [x.bfloat16().cuda() for x in (q, k, v)]
-        many = [x.repeat(n, 1, 1) for x in one]
-        got = []
-        for cnt, t in ((1, one), (n, many)):
-            cu = torch.arange(0, T * cnt + 1, T, dtype=torch.int32, device="cuda")
+        first = None
+        for n in counts:
+            t = [x.repeat(n, 1, 1) for x in one]
+            cu = torch.arange(0, T * n + 1, T, dtype=torch.int32, device="cuda")
             out, lse = torch.zeros_like(t[0]), torch.zeros(t[0].shape[:2], dtype=torch.float32, device="cuda")
-            sx.full_attn(desc, *t, cu, cnt, T, out, lse)
+            sx.full_attn(desc, *t, cu, n, T, out, lse)
             torch.cuda.synchronize()
-            got.append((out, lse))
-        (a, la), (b, lb) = got
-        for r in (0, n - 1):
-            for x, y in ((a, b[r * T:(r + 1) * T]), (la, lb[r * T:(r + 1) * T])):
-                assert torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(7.0), y.nan_to_num(7.0)), (steps, odd)
+            first = first or (out, lse)
+            for r in (0, n - 1):
+                for x, y in ((out, first[0]), (lse, first[1])):
+                    x = x[r * T:(r + 1) * T]
+                    assert torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(7.0), y.nan_to_num(7.0)), (n, steps, odd)
+        a = first[0]
         if odd is None and steps[0][1] > -1e30:
             z = torch.einsum("ihd,jhd->hij", one[0].double().cpu(), one[1].double().cpu().repeat_interleave(hq // hkv, 1)) * d ** -0.5
             z.masked_fill_(torch.ones(T, T, dtype=torch.bool).triu(1), -float("inf"))
