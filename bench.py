@@ -82,9 +82,11 @@ KERNELS = {
     "attn_mfma_kernel<128, false, true, true>": ("sx_full_attn", "k_attn.hip", True),
     "attn_mfma_kernel<128, false, true, false>": ("sx_full_attn", "k_attn.hip", True),   # (under graph capture)
     # few query rows
-    "attn_short_kernel<128, true, true>": ("sx_sparse_attn", "k_attn_short.hip", True),
-    "attn_short_kernel<128, false, true>": ("sx_full_attn", "k_attn_short.hip", True),
-    "attn_short_kernel<128, true, false>": ("sx_sparseq_score", "k_attn_short.hip", False),
+    "attn_short_kernel<128, true, 8>": ("sx_sparse_attn", "k_attn_short.hip", True),
+    "attn_short_kernel<128, true, 4>": ("sx_sparse_attn", "k_attn_short.hip", True),
+    "attn_short_kernel<128, false, 8>": ("sx_full_attn", "k_attn_short.hip", True),
+    "attn_short_kernel<128, false, 4>": ("sx_full_attn", "k_attn_short.hip", True),
+    "lse_short_kernel<128>": ("sx_sparseq_score", "k_attn_short.hip", False),
     # two-pass scoring only (layers without a preceding full layer)
     "attn_mfma_kernel<128, true, false, false>": ("sx_sparseq_score", "k_attn.hip", False),
     "lse_merge_kernel": ("sx_sparseq_score", "k_attn.hip", False),
