@@ -539,7 +539,9 @@ hipError_t launch_d(const AttnLaunch& L, bool paged, hipStream_t s) {
 // 6000 110 / 92, 304 of 6000 114 / 135.  The log-sum-exp pass of the 256-column kernel splits the keys too
 // and reads K only, so it is left earlier: 32 items of 1000 keys 67 / 52, 96 of 3000 112 / 113, 256 of 8192
 // 279 / 318 us.
+// (The request is a grid dimension here, of at most 65535; the 256-column grid has no such bound.)
 bool attn_short_fits(const AttnLaunch& L) {
+  if (L.n_req > 65535) return false;
   const int rpw = 256 / (L.Hq / L.Hkv);
   const int64_t items = (int64_t)(L.grid_rows + rpw - 1) / rpw * L.Hkv * L.n_req * L.D / 128;
   return items <= (!L.out ? 20 : L.D == 128 ? 140 : 90) + 80000 / std::max(1, L.max_keys);

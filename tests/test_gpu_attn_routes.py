@@ -122,3 +122,17 @@ def test_replays_and_repeats_are_identical(hq, hkv, d, lengths):
         n = min(cut, n_rows[r])
         assert (part[off + n:w.token_offsets[r + 1]] == 7.0).all()
         assert (part[off:off + n].float() - first[0][off:off + n].float()).abs().max() <= 2e-2
+
+
+def test_more_requests_than_a_grid_dimension_holds():
+    """70000 one-token requests: few enough items for the 32-column workgroups, too many requests for their grid.
+    One key has probability 1, so an output is its value."""
+    log("[attn routes] 70000 requests")
+    n, d = 70000, 64
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q, v = (torch.randn((n, h, d), generator=gen, device="cuda").bfloat16() for h in (2, 1))
+    cu = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    out = torch.zeros_like(q)
+    sx.full_attn(sx.make_desc(2, 1, d, "bf16", 1e4), q, v, v, cu, n, 1, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, v.expand_as(out))
