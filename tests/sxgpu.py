@@ -108,6 +108,32 @@ class GpuLayer:
         self.n_rows.copy_(torch.from_numpy(n))
 
 
+def _cu():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def attention_route(rows, keys, requests, hq, hkv, d):
+    """The kernel that the library's rule gives a bfloat16 attention of at most so many rows and keys per request:
+    the 256-column grid (0), or workgroups of so many waves for 32 columns."""
+    g = hq // hkv
+    rpw = 256 // g
+    if -(-rows // rpw) * hkv * requests * d // 128 > (140 if d == 128 else 90) + 80000 // max(1, keys):
+        return 0
+    groups = (rows // rpw * -(-rpw * g // 32) + -(-(rows % rpw) * g // 32)) * hkv * requests
+    return 8 if 2 * groups <= 3 * _cu() else 2 if d == 64 and groups > 4 * _cu() else 4
+
+
+def lse_route(rows, keys, requests, hq, hkv, d):
+    """The same for the log-sum-exp pass of at most so many probe rows: 4, or 0 and the grid's key pieces."""
+    tiles = -(-rows // (256 // (hq // hkv))) * hkv * requests
+    if tiles * d // 128 <= 20 + 80000 // max(1, keys):
+        return 4, 1
+    pieces = 1
+    while pieces < 4 and tiles * pieces < 1024:
+        pieces *= 2
+    return 0, pieces
+
+
 def oracle_pool(w):
     return np.full(pool_shape(w, w.n_dst_blocks), CANARY, dtype=np.float32)
 

@@ -9,7 +9,7 @@ import torch
 
 import oracle as O
 import workloads as W
-from sxgpu import GpuLayer, desc_of, dev, host, log
+from sxgpu import GpuLayer, attention_route, desc_of, dev, host, log, lse_route
 
 pytestmark = pytest.mark.gpu
 
@@ -28,12 +28,12 @@ def _work(hq, hkv, d, lengths, seed=0):
     return W.custom_workload(specs, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype="bf16", rope_base=1e4, seed=seed)
 
 
-# (q heads, kv heads, d, request lengths): 1 to 33 columns, group sizes that do not divide 32, one to five
-# 32-key pieces per wave; then launches of 256-column workgroups (more than 140 items), with and
-# without requests of few rows beside them
+# (q heads, kv heads, d, request lengths): 1 to 33 columns, group sizes that do not divide 32, one key to several
+# rounds; then launches of the 256-column grid in all three passes (full, sparse, log-sum-exp), the
+# longest request's log-sum-exps in pieces of keys, with requests of few rows beside them
 SHORT = [(8, 2, 64, (1, 4, 5, 8, 9)), (7, 1, 128, (37, 1)), (8, 8, 64, (15, 16, 17, 31, 33)), (28, 4, 128, (70, 129)),
          (33, 1, 64, (63, 2)), (64, 1, 128, (31,)), (8, 2, 128, (127, 128, 385, 640))]
-LONG = [(32, 8, 128, (600, 500, 550, 3)), (64, 16, 64, (700, 650))]
+LONG = [(32, 8, 128, (2100, 600, 500, 3)), (64, 16, 64, (2100, 650, 640)), (28, 4, 64, (2100, 1900, 700, 900))]
 
 
 @pytest.mark.parametrize("hq,hkv,d,lengths", SHORT + LONG, ids=lambda x: str(x).replace(" ", ""))
@@ -53,6 +53,13 @@ def test_attention_routes(hq, hkv, d, lengths):
     g.scatter_rows(0.2)
     g.attend(0.2)
     torch.cuda.synchronize()
+    n, most, bound = len(lengths), max(lengths), g.plan.budget(0.2)[1]
+    probes = max(len(O.probe_positions(r.n_tokens, r.segments)) for r in w.requests)
+    routes = attention_route(most, most, n, hq, hkv, d), attention_route(bound, most, n, hq, hkv, d), lse_route(probes, most, n, hq, hkv, d)
+    if (hq, hkv, d, lengths) in LONG:
+        assert routes[:2] == (0, 0) and routes[2][0] == 0 and routes[2][1] > 1
+    else:
+        assert all(routes[:2]) and routes[2] == (4, 1)
     got, glse, sparse, scores = host(out), host(lse), host(g.out), host(g.scores)
     rows, n_rows, kc, vc = g.rows.cpu().numpy(), g.n_rows.cpu().numpy(), host(g.k_cache), host(g.v_cache)
     scale = O.softmax_scale(d)
@@ -76,7 +83,7 @@ def test_attention_routes(hq, hkv, d, lengths):
         assert abs(scores[off:off + T].sum() - hq * len(probes)) <= 1e-3 * hq * len(probes)
 
 
-@pytest.mark.parametrize("hq,hkv,d,lengths", [SHORT[3], SHORT[-1], LONG[0]], ids=lambda x: str(x).replace(" ", ""))
+@pytest.mark.parametrize("hq,hkv,d,lengths", [SHORT[3], SHORT[-1], LONG[0], LONG[1]], ids=lambda x: str(x).replace(" ", ""))
 def test_replays_and_repeats_are_identical(hq, hkv, d, lengths):
     """Graph replays with eager calls between them, all equal to the first eager result; a row list cut by
     max_rows leaves the further rows alone."""

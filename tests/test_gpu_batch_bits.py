@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import workloads as W
-from sxgpu import GpuLayer, desc_of, log
+from sxgpu import GpuLayer, attention_route, desc_of, log
 
 pytestmark = pytest.mark.gpu
 
@@ -75,18 +75,6 @@ def test_float32_tile_width(hq, hkv, d, lengths):
     _attention_bits(_work(hq, hkv, d, lengths, "f32"), lambda rows, keys, n: (rows * g + 31) // 32 * hkv * n >= 256)
 
 
-def attention_route(rows, keys, requests, hq, hkv, d):
-    """The kernel of a bfloat16 attention of so many rows per request: the 256-column grid (0), or workgroups of
-    so many waves for 32 columns."""
-    rpw = 256 // (hq // hkv)
-    tiles = -(-rows // rpw) * hkv * requests
-    if tiles * d // 128 > (140 if d == 128 else 90) + 80000 // max(1, keys):
-        return 0
-    cu, g = torch.cuda.get_device_properties(0).multi_processor_count, hq // hkv
-    groups = (rows // rpw * -(-rpw * g // 32) + -(-(rows % rpw) * g // 32)) * hkv * requests
-    return 8 if 2 * groups <= 3 * cu else 2 if d == 64 and groups > 4 * cu else 4
-
-
 # the request alone in 32-column workgroups of eight or four waves, the batch in the 256-column grid, and at the end
 # in those of four and two waves: group sizes that do and do not divide 256 and 32, both head dims, partial last
 # rounds (256, 128 and 64 keys) and key tiles
@@ -98,6 +86,39 @@ def attention_route(rows, keys, requests, hq, hkv, d):
 def test_bfloat16_attention(hq, hkv, d, lengths):
     log(f"[batch bits] bf16 {hq}/{hkv}/{d} {lengths}")
     _attention_bits(_work(hq, hkv, d, lengths, "bf16"), lambda rows, keys, n: attention_route(rows, keys, n, hq, hkv, d))
+
+
+@pytest.mark.parametrize("hq,hkv,d,T,below", [(32, 8, 128, 1537, 1536), (16, 16, 64, 6000, 3072)], ids=["d128", "d64"])
+def test_bfloat16_attention_at_the_rule(hq, hkv, d, T, below):
+    """The last bound that goes to 32-column workgroups and the next, for full attention (with a request of T rows
+    in the second call only) and for sparse attention."""
+    log(f"[batch bits] at the rule {hq}/{hkv}/{d}")
+    assert attention_route(below, T, 1, hq, hkv, d) and not attention_route(below + 1, T, 1, hq, hkv, d)
+    n = below + 1 - 40
+    w = W.custom_workload([[(T, False, 0, None)]], n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype="bf16", rope_base=1e4, seed=d)
+    g = GpuLayer(w, W.layer_tensors(w, 0))
+    sx.kv_scatter(g.plan, g.t["k"], g.t["v"], g.k_cache, g.v_cache)
+    g.set_rows([np.arange(T - n, T)])
+    out = []
+    for bound in (below, below + 1):
+        o = torch.zeros_like(g.out)
+        sx.sparse_attn(g.plan, g.t["q"], g.rows, g.n_rows, bound, g.k_cache, g.v_cache, o)
+        out.append(o)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1]) and out[0][:n].any(-1).all()
+    # full attention takes its longest request as the number of keys too
+    last = max(t for t in range(1, T) if attention_route(t, t, 1, hq, hkv, d))
+    assert not attention_route(last + 1, last + 1, 1, hq, hkv, d)
+    out = []
+    for t in (last, last + 1):
+        cu = torch.tensor([0, t], dtype=torch.int32, device="cuda")
+        o = torch.zeros_like(g.out)
+        sx.full_attn(desc_of(w), g.t["q"], g.t["k"], g.t["v"], cu, 1, t, o)
+        out.append(o)
+    torch.cuda.synchronize()
+    rpw = 256 // (hq // hkv)
+    same = last // rpw * rpw      # the rows of the row tiles that both calls fill
+    assert torch.equal(out[0][:same], out[1][:same]) and out[1][:last + 1].any(-1).all()
 
 
 # requests per launch: workgroups of eight, four and (d = 64) two waves, and the 256-column grid

@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 try:
     import paper_2606_01751_amd as sx
-    from sxgpu import GpuLayer, desc_of, dev, log
+    from sxgpu import GpuLayer, attention_route, desc_of, dev, log
 except Exception:  # pragma: no cover - collected without the library
     sx = None
 
@@ -32,16 +32,22 @@ def _need_gpu():
     sx.lib()
 
 
-def _workload():
-    """Three requests (700, 257 and 1300 tokens), 8 query heads over 2 KV heads, d = 128, bf16."""
+@pytest.fixture(params=[(32, 8, 128), (64, 16, 64)], ids=["d128", "d64"])
+def w(request):
+    """Three requests (1700, 513 and 2600 tokens), bf16, large enough that every launch below, the first request's
+    own among them, goes to the 256-column grid."""
+    hq, hkv, d = request.param
     rng = np.random.default_rng(11)
-    specs = [W.random_request_specs(rng, T, max_seg=90) for T in (700, 257, 1300)]
-    return W.custom_workload(specs, n_q_heads=8, n_kv_heads=2, head_dim=128, dtype="bf16", rope_base=1e4,
+    specs = [W.random_request_specs(rng, T, max_seg=90) for T in (1700, 513, 2600)]
+    return W.custom_workload(specs, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype="bf16", rope_base=1e4,
                              rope_style="neox", seed=11, plant_per_segment=3, name="persist")
 
 
-def test_full_attention_graph_replays_and_two_streams():
-    w = _workload()
+def _on_the_grid(w, rows, requests, keys=None):
+    assert attention_route(rows, keys or rows, requests, w.n_q_heads, w.n_kv_heads, w.head_dim) == 0
+
+
+def test_full_attention_graph_replays_and_two_streams(w):
     log("[persistent] full attention: eager, 3 graph replays, two streams")
     t = W.layer_tensors(w, 0)
     q, k, v = dev(t["q"], w), dev(t["k"], w), dev(t["v"], w)
@@ -50,6 +56,8 @@ def test_full_attention_graph_replays_and_two_streams():
     # the first request alone: a launch of another size between the replays
     cu1 = torch.tensor(w.token_offsets[:2], dtype=torch.int32, device="cuda")
     t1 = w.requests[0].n_tokens
+    _on_the_grid(w, max_t, n_req)
+    _on_the_grid(w, t1, 1)
 
     def run(out, stream=None):
         sx.full_attn(desc_of(w), q, k, v, cu, n_req, max_t, out, stream=stream)
@@ -86,8 +94,7 @@ def test_full_attention_graph_replays_and_two_streams():
     assert torch.equal(o1, want) and torch.equal(o2, want)
 
 
-def test_sparse_attention_graph_replays_and_fewer_rows():
-    w = _workload()
+def test_sparse_attention_graph_replays_and_fewer_rows(w):
     log("[persistent] sparse attention: eager, 3 graph replays, calls with fewer rows between them")
     g = GpuLayer(w, W.layer_tensors(w, 0))
     ratio = 0.3
@@ -97,6 +104,7 @@ def test_sparse_attention_graph_replays_and_fewer_rows():
     g.select(ratio)
     g.scatter_rows(ratio)
     m = g.plan.budget(ratio)[1]
+    _on_the_grid(w, m, len(w.requests), max(r.n_tokens for r in w.requests))
 
     def run(out, n_rows, stream=None):
         sx.sparse_attn(g.plan, g.t["q"], g.rows, n_rows, m, g.k_cache, g.v_cache, out, stream=stream)
@@ -127,11 +135,10 @@ def test_sparse_attention_graph_replays_and_fewer_rows():
             assert not fewer[b:offs[r] + int(n[r])].any(), f"request {r}: rows past the bound written"
 
 
-def test_sparse_attention_planned_tile_order():
+def test_sparse_attention_planned_tile_order(w):
     """sx_rows_mask plans the order in which sx_sparse_attn takes its row tiles for the same row list;
     the result must not change, also when n_rows changes at the same address after the plan was
     made (the attention then sees a different tile count and keeps the queue's own order)."""
-    w = _workload()
     log("[persistent] sparse attention with the planned tile order of sx_rows_mask")
     g = GpuLayer(w, W.layer_tensors(w, 0))
     ratio = 0.3
@@ -141,6 +148,7 @@ def test_sparse_attention_planned_tile_order():
     g.select(ratio)
     g.scatter_rows(ratio)
     m = g.plan.budget(ratio)[1]
+    _on_the_grid(w, m, len(w.requests), max(r.n_tokens for r in w.requests))
     want = torch.zeros_like(g.out)
     sx.sparse_attn(g.plan, g.t["q"], g.rows, g.n_rows, m, g.k_cache, g.v_cache, want)
     mask = torch.zeros(w.total_tokens, dtype=torch.uint8, device="cuda")
@@ -162,12 +170,11 @@ def test_sparse_attention_planned_tile_order():
         assert not out[b:offs[r] + int(n[r])].any()
 
 
-def test_many_launches_cycle_every_queue_slot():
+def test_many_launches_cycle_every_queue_slot(w):
     """70 full-attention launches (more than the 64 library queue slots, so every slot is reused)
     of three sizes in turn, and 30 sparse-attention launches on one plan with three row counts in
     turn: every result is bit-identical to the first one of its size, so each launch left its
     counters at zero."""
-    w = _workload()
     log("[persistent] 70 full-attention and 30 sparse-attention launches in turn")
     t = W.layer_tensors(w, 0)
     q, k, v = dev(t["q"], w), dev(t["k"], w), dev(t["v"], w)
@@ -178,6 +185,7 @@ def test_many_launches_cycle_every_queue_slot():
               max(r.n_tokens for r in w.requests[:i + 1])) for i in range(n_req)]
     want = []
     for cu, nr, mx in sizes:
+        _on_the_grid(w, mx, nr)
         o = torch.zeros_like(q)
         sx.full_attn(desc_of(w), q, k, v, cu, nr, mx, o)
         want.append(o)
@@ -199,6 +207,7 @@ def test_many_launches_cycle_every_queue_slot():
     g.select(ratio)
     g.scatter_rows(ratio)
     m = g.plan.budget(ratio)[1]
+    _on_the_grid(w, m, len(w.requests), max(r.n_tokens for r in w.requests))
     n = g.n_rows.cpu().numpy()
     counts = [torch.from_numpy(np.maximum(n // d, 1).astype(np.int32)).to("cuda") for d in (1, 2, 3)]
     ref = []
@@ -215,3 +224,54 @@ def test_many_launches_cycle_every_queue_slot():
     torch.cuda.synchronize()
     for i, o in enumerate(outs):
         assert torch.equal(o, ref[i % 3]), f"sparse-attention launch {i}"
+
+
+# key-value heads (32 workgroups per head at 8, 64 at 4, no plan for more: 2)
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (28, 4), (16, 2)])
+def test_every_planned_order_takes_every_tile_once(hq, hkv):
+    """The order that sx_rows_mask plans for row counts that leave fewer tiles than workgroups, as many, a few more
+    and several times as many, all of one cost and of very different ones; and for a count that changed
+    after planning.  Against the same calls on a plan without an order, bit for bit: a tile taken twice or
+    left out would show in the rows that it has to write."""
+    log(f"[persistent] planned orders {hq}/{hkv}")
+    lengths = (6000, 300, 5000)
+    w = W.custom_workload([[(T, False, 0, None)] for T in lengths], n_q_heads=hq, n_kv_heads=hkv, head_dim=64, dtype="bf16",
+                          rope_base=1e4, seed=2)
+    g = GpuLayer(w, W.layer_tensors(w, 0))
+    sx.kv_scatter(g.plan, g.t["k"], g.t["v"], g.k_cache, g.v_cache)
+    other = sx.Plan(desc_of(w), w.requests, w.n_dst_blocks, w.n_src_blocks)
+    bound, rpw = max(lengths), 256 // (hq // hkv)
+    _on_the_grid(w, bound, len(lengths))
+    per_head = torch.cuda.get_device_properties(0).multi_processor_count // hkv
+    rng = np.random.default_rng(3)
+
+    def some(n, T):      # n rows, the last ones or spread
+        return np.sort(rng.choice(T, size=n, replace=False))
+
+    tiles = lambda n: min(n * rpw, lengths[0])
+    sets = [
+        [some(1, 6000), some(0, 300), some(1, 5000)],                                   # two tiles
+        [some(tiles(per_head - 1), 6000), some(1, 300), some(0, 5000)],                 # one per workgroup
+        [some(tiles(per_head), 6000), some(1, 300), some(1, 5000)],                     # a few more
+        [np.arange(6000), np.arange(300), np.arange(5000)],                             # several, falling costs
+        [np.arange(6000 - 5 * rpw, 6000), some(0, 300), np.arange(5000 - 5 * rpw, 5000)],   # two costs, tied
+        [np.arange(5), np.arange(5), np.arange(5)],                                     # all alike
+        [some(0, 6000), some(0, 300), some(0, 5000)],                                   # nothing
+    ]
+    mask = torch.zeros(w.total_tokens, dtype=torch.uint8, device="cuda")
+    for i, rows in enumerate(sets):
+        g.set_rows(rows)
+        sx.rows_mask(g.plan, g.rows, g.n_rows, bound, mask)
+        for fewer in (0, 1, 300):
+            g.n_rows.copy_(torch.tensor([max(0, len(r) - fewer) for r in rows], dtype=torch.int32))
+            out = []
+            for plan in (g.plan, other):
+                o = torch.zeros_like(g.out)
+                sx.sparse_attn(plan, g.t["q"], g.rows, g.n_rows, bound, g.k_cache, g.v_cache, o)
+                out.append(o)
+            torch.cuda.synchronize()
+            assert torch.equal(out[0], out[1]), (i, fewer)
+            for off, r in zip(w.token_offsets, rows):
+                n = max(0, len(r) - fewer)
+                assert out[0][off:off + n].any(-1).all() and not out[0][off + n:off + len(r)].any(), (i, fewer)
+    other.close()

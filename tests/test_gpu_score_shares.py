@@ -9,7 +9,7 @@ import torch
 
 import oracle as O
 import workloads as W
-from sxgpu import GpuLayer, host, log
+from sxgpu import GpuLayer, host, log, lse_route
 
 pytestmark = pytest.mark.gpu
 
@@ -20,7 +20,8 @@ except Exception:  # pragma: no cover
 
 # (q heads, kv heads, d, pieces per request): one share (few chunks), shares of two chunks, a last share
 # with a partial chunk or with none, tiles that no probe row but the last sees, G not dividing 64, and a
-# plan with enough tiles for fewer shares
+# plan with enough tiles for fewer shares; the last probe row count whose log-sum-exps go to 32-column workgroups
+# and the next (d = 128, d = 64)
 CASES = [
     (8, 2, 128, [[(5, False), (40, True)]]),
     (32, 8, 128, [[(33, False), (300, True), (31, False)]]),
@@ -28,6 +29,10 @@ CASES = [
     (8, 8, 64, [[(300, True), (259, False), (300, True), (1, False)]]),
     (64, 1, 64, [[(100, True), (37, False)]]),
     (16, 2, 128, [[(64, False), (1500, True), (400, False)], [(257, True)], [(255, False), (2, True)]]),
+    (32, 8, 128, [[(768, False), (232, True)]]),
+    (32, 8, 128, [[(769, False), (231, True)]]),
+    (32, 16, 64, [[(1024, False), (576, True)]]),
+    (32, 16, 64, [[(1025, False), (575, True)]]),
 ]
 
 
@@ -65,3 +70,9 @@ def test_scores(hq, hkv, d, pieces, one_pass):
     if one_pass:
         sx.sparseq_score_static(g.plan, g.t["q"], g.k_cache, g.scores, lse)
         assert np.array_equal(host(g.scores), first)
+
+
+def test_log_sum_exp_pairs_lie_on_both_sides_of_the_rule():
+    for (hq, hkv, d, (a,)), (_, _, _, (b,)) in ((CASES[-4], CASES[-3]), (CASES[-2], CASES[-1])):
+        T = sum(n for n, _ in a)
+        assert lse_route(a[0][0], T, 1, hq, hkv, d)[0] == 4 and lse_route(b[0][0], T, 1, hq, hkv, d)[0] == 0
