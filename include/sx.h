@@ -53,6 +53,12 @@
  *   out (full)            [sum T][Hq][d]
  * Query head h reads KV head h / (Hq / Hkv).  Causality is by token index; RoPE positions
  * (old_pos/new_pos) are used only by the re-alignment.
+ *
+ * Results: a call gives the same bits every time.  A request's results also do not depend on the
+ * other requests of the plan or call, nor on how loose max_rows and max_seqlen are, although the
+ * size of a launch chooses kernels and tiles -- with one exception: bfloat16 scores
+ * (sx_sparseq_score) may differ in the last places between plans, whose size sets the pieces of
+ * keys of the log-sum-exps and the shares of the probe rows that are added up.
  */
 #ifndef SX_H
 #define SX_H
@@ -222,11 +228,12 @@ sx_status sx_realign_scatter_layers(const sx_plan* plan, int32_t n_layers, const
  * sx_realign_scatter_masked: mask[off_r + t] = 1 for every listed row t of request r
  * (rows[off_r .. off_r + min(n_rows[r], max_rows))), 0 for every other token of the plan.
  * mask is caller-owned DEVICE memory of sum T bytes; rows/n_rows/max_rows as in sx_kv_scatter.
- * Listed values outside [0, T_r) are ignored.  No host sync.  bfloat16 plans: the same launch
- * plans, in the plan's scratch, the order in which sx_sparse_attn takes its row tiles (Multifit
- * over their estimated costs); sx_sparse_attn uses it when called with the same rows, n_rows and
- * max_rows, as the sparse layers that share R are (Section 3.4).  The order changes only which
- * workgroup computes a row tile, never a result. */
+ * Listed values outside [0, T_r) are ignored.  One launch up to max_rows
+ * 16384, beyond that one that clears and one that marks.  No host sync.  bfloat16 plans: the same
+ * launch, or a third, plans in the plan's scratch the order in which sx_sparse_attn takes its row
+ * tiles (Multifit over their estimated costs); sx_sparse_attn uses it when called with the same
+ * rows, n_rows and max_rows, as the sparse layers that share R are (Section 3.4).  The order changes
+ * only which workgroup computes a row tile, never a result. */
 sx_status sx_rows_mask(const sx_plan* plan, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
                        uint8_t* mask, void* stream);
 
@@ -246,8 +253,8 @@ sx_status sx_realign_scatter_masked(const sx_plan* plan, const void* src_k, cons
  *   scores[off_r + j] = sum_h sum_{i in P_r, i >= j} softmax_j(scale * q[i,h] . K[j, h/(Hq/Hkv)])
  * over the probe rows P_r = I_nr U S_tail of request r, reading keys from k_cache (whatever the
  * cache holds: re-aligned cached keys and the fresh keys written so far).  Probabilities and
- * sums are float32 per tile and float64 across tiles; the order of every sum is fixed, so the
- * result is deterministic.  Positions after the last probe get 0.  Uses plan scratch.
+ * sums are float32 per tile and float64 across tiles; the order of every sum is fixed for a plan, so
+ * the result is deterministic.  Positions after the last probe get 0.  Uses plan scratch.
  * lse_in: NULL (two passes over the keys: the softmax denominators of the probe rows, then the
  *   column sums), or a DEVICE float32 array [sum T][Hq] of natural-log sums
  *   log sum_{j <= i} exp(scale * q[i,h] . K[j]) over the keys k_cache holds -- exactly what
@@ -281,7 +288,7 @@ sx_status sx_topk_select(const sx_plan* plan, const float* scores, double ratio,
 /* Algorithm 1 step 21: for every listed row i of request r and every query head h,
  *   out[off_r + n, h] = sum_{j <= i} softmax_j(scale * q[off_r + i, h] . K[j]) V[j]
  * with K/V read from the paged cache of request r.  bfloat16 runs on matrix cores with float32
- * accumulation and bfloat16 probabilities; float32 runs on vector ALUs.  max_rows as in
+ * accumulation and bfloat16 probabilities, float32 on the float32 matrix cores.  max_rows as in
  * sx_kv_scatter: the rows n >= min(n_rows[r], max_rows) are neither computed nor written, so the
  * attention covers exactly the rows whose K/V sx_kv_scatter writes for the same list.  Uses the
  * plan's work-queue counters (bfloat16), so calls sharing a plan must be stream-ordered; takes its
@@ -336,7 +343,8 @@ sx_status sx_gemm_rows_split(const sx_plan* plan, const int32_t* rows, const int
                              const int32_t* part_n, void* const* y_parts, int32_t y_by_token, void* stream);
 
 /* RMSNorm: y[row] = x[row] / sqrt(mean_j x[row][j]^2 + eps) * gamma, rows of h elements
- * (h a multiple of 8), gamma [h]; formed in float64 in a fixed order and rounded once. */
+ * (h a multiple of 8), gamma [h]; formed in float64 in a fixed order, rounded to float32 and
+ * from there to bfloat16. */
 sx_status sx_rmsnorm_rows(const sx_plan* plan, const int32_t* rows, const int32_t* n_rows, int32_t max_rows,
                           const void* x, int32_t x_by_token, const void* gamma, float eps, int32_t h, void* y,
                           int32_t y_by_token, void* stream);

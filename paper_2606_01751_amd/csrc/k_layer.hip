@@ -283,7 +283,7 @@ __global__ __launch_bounds__(WN * WM * 64, 1) void gemm_rows_kernel(GemmRowsK a)
 // RMSNorm of listed rows: one workgroup per row, the row read once into registers (NC 16-byte pieces
 // per thread; longer rows read their further pieces again), sum of squares in a fixed order (thread,
 // wave, waves in order).  Sum and products in float64, which hides under the row's transfers and leaves
-// one rounding, to bf16 by way of float32: a float32 product near a rounding boundary of bf16 is off by
+// the rounding to float32 and from there to bf16: a float32 product near a rounding boundary of bf16 is off by
 // a whole unit for every later reader of the row.  Bound by HBM, for few rows by the latency of one read: 394 rows of
 // 4096 5.3 us, 6750 rows 23 us; one wave per row reading it twice took 9.2 and 28.5.
 // ---------------------------------------------------------------------------------------------

@@ -1,6 +1,7 @@
 """Selection, and row masks on both sides of their one-launch limit (GPU), exact against the oracle.
 
-A row list of up to 16384 rows is masked in one launch, by workgroups of 8192 tokens; a longer one in two.
+A row list of up to 16384 rows is masked in one launch, by workgroups of 8192 tokens, bfloat16 plans with the tile
+order in the same; a longer one in a clearing and a marking launch, and the order in a third.
 """
 import types
 
