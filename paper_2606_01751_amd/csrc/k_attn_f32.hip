@@ -26,9 +26,6 @@ namespace sx {
 namespace {
 
 constexpr int FW = 8;     // waves per workgroup
-// Grid: x = KV head fastest, then kTilesX tiles; y = further tiles; z = request.  With the KV head
-// fastest the round-robin dispatch over the 8 XCDs keeps a head's K and V in one L2 (8 heads) or a few.
-constexpr int kTilesX = 64;
 constexpr int kWideTiles = 256;   // 32-column tiles from which the attention uses them (one per compute unit)
 
 struct AttnF {
@@ -80,8 +77,8 @@ struct Tile {
 // 32 columns of 1500 keys at D = 64 take it 20 us, so launches of few tiles use 16 columns, which
 // doubles the K/V reads per column (see the dispatch).
 // Measured: 1500 tokens, 576 rows, 8/2/64 27 us (237 with one wave per row and head on the vector
-// ALU), the 192 probe rows of a 512-token layer 8.6 us (20), 4096 rows of 32/8/128 1.42 ms or
-// 97 TFLOP/s (29 ms).  expf takes 6 % of that over v_exp_f32 of x log2 e with the product's rounding made up
+// ALU), the 192 probe rows of a 512-token layer 8.6 us (20), 4096 rows of 32/8/128 1.45 ms or
+// 95 TFLOP/s (29 ms).  expf takes 6 % of that over v_exp_f32 of x log2 e with the product's rounding made up
 // for, which is as exact for probabilities near 1 but drops those below 2^-126.
 template <int D, int CT, bool PAGED, bool PV>
 __global__ __launch_bounds__(FW * 64, 1) void attn_f32_kernel(AttnF a) {
@@ -498,8 +495,8 @@ hipError_t launch_attn_f32(const AttnLaunch& L, bool paged, hipStream_t s) {
   a.scale = L.scale;
   // 32 columns per workgroup read each K/V row half as often; 16 columns give twice the workgroups and
   // halve the longest one, which is what bounds a launch with fewer tiles than compute units.  Measured
-  // (whole layer calls, 16 / 32 columns): 150 tiles 28 / 42 us, 175 28 / 38, 250 24 / 29; 400 96 / 95,
-  // 600 78 / 66, 4096 497 / 401 us
+  // (calls, 16 / 32 columns): 144 tiles 27 / 41 us, 250 38 / 52; 304 41 / 34, 400 80 / 74, 600 121 / 109, 4096
+  // 1627 / 1455 us
   const bool wide = ((int64_t)L.grid_rows * a.G + 31) / 32 * L.Hkv * L.n_req >= kWideTiles;
   const int ct = wide ? 32 : 16;
   const dim3 grid = grid_of(((int64_t)L.grid_rows * a.G + ct - 1) / ct, L.Hkv, L.n_req);

@@ -19,9 +19,6 @@
 namespace sx {
 namespace {
 
-// Grid: x = KV head fastest, then kTilesX tiles; y = further tiles; z = request.  With the KV head
-// fastest the round-robin dispatch over the 8 XCDs keeps a head's K and V in one L2 (8 heads) or a few.
-constexpr int kTilesX = 64;
 constexpr int COLS = 256;   // columns of a row tile of k_attn.hip
 constexpr int SW = 4;       // waves per workgroup of the log-sum-exp pass
 

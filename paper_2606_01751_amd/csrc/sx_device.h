@@ -120,6 +120,11 @@ __device__ __forceinline__ void sched_pipelined() {
   SX_SG(kSgMfma, PRE);
 }
 
+// Grid of the kernels that tile one request's columns: x = KV head fastest, then kTilesX tiles; y = further
+// tiles; z = request.  With the KV head fastest the round-robin dispatch over the 8 XCDs keeps a head's
+// K and V in one L2 (8 heads) or a few.
+constexpr int kTilesX = 64;
+
 // Pool offset (elements) of (slot, head) in a [blocks][Hkv][16][D] pool.
 __device__ __forceinline__ int64_t pool_off(int32_t slot, int head, int Hkv, int D) {
   return ((((int64_t)(slot >> 4)) * Hkv + head) * 16 + (slot & 15)) * (int64_t)D;
