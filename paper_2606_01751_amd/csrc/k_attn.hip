@@ -1008,11 +1008,12 @@ __global__ __launch_bounds__(256) void probe_gather_kernel(const uint16_t* __res
 // issued two chunks ahead.  No global load in the loop feeds an address, so the loop waits only for
 // transfers issued two chunks earlier.
 // Bound by MFMAs and vector issue (one exponential per pair), which add up on a SIMD instead of running
-// beside each other: each of two workgroups on a compute unit takes 4070 cycles per chunk, in which the
-// SIMD's four waves have 2050 of MFMAs and 2070 of vector issue; and, for few tiles, by the longest workgroup.  128 registers and 50 KB of LDS let two workgroups
-// share a compute unit, each covering the other's barriers: that beats two key tiles per wave (half the
-// probe-column reads, 228 registers, one workgroup), 361 -> 307 us at 32768 tokens with 2048 probe rows
-// and 1926 -> 1724 us for eight requests of 120000 tokens; with the shares 171 -> 115 us at 8192 tokens.
+// beside each other (each of two workgroups on a compute unit takes 4070 cycles per chunk, in which the
+// SIMD's four waves have 2050 of MFMAs and 2070 of vector issue), and, for few tiles, by the longest
+// workgroup.  128 registers and 50 KB of LDS let two workgroups share a compute unit, each covering the
+// other's barriers: that beats two key tiles per wave (half the probe-column reads, 228 registers, one
+// workgroup), 361 -> 307 us at 32768 tokens with 2048 probe rows and 1926 -> 1724 us for eight requests of
+// 120000 tokens; with the shares 171 -> 115 us at 8192 tokens.
 struct ColsumK {
   const uint16_t* k;
   const uint16_t* qp;

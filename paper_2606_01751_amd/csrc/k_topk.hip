@@ -601,12 +601,12 @@ constexpr int N1 = 1024, W1 = N1 / 64;
 constexpr int RT = N1 * TPT;   // tokens per round
 template <int R>
 __global__ __launch_bounds__(N1) void topk_one_kernel(TopkArgs a) {
-  constexpr int P = (R + 1) / 2;   // words of a scan: the counts of two rounds (at most 8192 each) share one
+  static_assert(R <= 2, "a scan word holds the counts (at most 8192 each) of two rounds");
   __shared__ __attribute__((aligned(16))) uint32_t hist[FINE / 2];   // bins 2 w and 2 w + 1 in the halves of word w
   __shared__ __attribute__((aligned(16))) uint32_t h[3][256];        // groups of 256 fine bins; second, third digit
   __shared__ int s_min[W1], s_max[W1];
   __shared__ int s_dig[3][3];
-  __shared__ int s_scan[2][P][W1];
+  __shared__ int s_scan[2][W1];
   static_assert(R * RT < 1 << 16 && RT < 1 << 16, "16-bit counts");
   const ReqDev rq = a.reqs[blockIdx.x];
   const int T = rq.T;
@@ -727,30 +727,22 @@ __global__ __launch_bounds__(N1) void topk_one_kernel(TopkArgs a) {
   }
   // rows of `mask` before this thread's in each round, in token order; returns their number
   auto place = [&](uint32_t mask, int slot, int (&at)[R]) {
-    int x[P], v[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      v[p] = __popc(mask >> (16 * p) & 0xff) | __popc(mask >> (16 * p) & 0xff00) << 16;
-      x[p] = wave_incl_sum(v[p]);
-      if (lane == 63) s_scan[slot][p][w] = x[p];
-    }
+    const int v = __popc(mask & 0xff) | __popc(mask & 0xff00) << 16;
+    const int x = wave_incl_sum(v);
+    if (lane == 63) s_scan[slot][w] = x;
     __syncthreads();
-    int sum = 0;
+    int before = 0, tot = 0;
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-      int before = 0, tot = 0;
-#pragma unroll
-      for (int i = 0; i < W1; ++i) {
-        const int y = s_scan[slot][p][i];
-        before += i < w ? y : 0;
-        tot += y;
-      }
-      before += x[p] - v[p];
-      at[2 * p] = sum + (before & 0xffff);
-      sum += tot & 0xffff;
-      if (2 * p + 1 < R) at[2 * p + 1 < R ? 2 * p + 1 : 0] = sum + (before >> 16);
-      sum += tot >> 16;
+    for (int i = 0; i < W1; ++i) {
+      const int y = s_scan[slot][i];
+      before += i < w ? y : 0;
+      tot += y;
     }
+    before += x - v;
+    const int first = tot & 0xffff;
+    at[0] = before & 0xffff;
+    if (R > 1) at[R - 1] = first + (before >> 16);
+    const int sum = first + (tot >> 16);
     return sum;
   };
   int at[R];
